@@ -161,9 +161,10 @@ struct KState {
   int32_t* mused;  // [B]
   int32_t* status; // [B]
   double* tau;     // [2][B]      adaptive steps: accepted step, suggested next step
+  double* smax;    // [m][B]      largest coefficient of the iterations before j (breakdown test)
 };
 
-inline size_t kstate_doubles(int m, int B) { return (size_t)B * (5 * m + 1 + 2 + 1 + 2); }
+inline size_t kstate_doubles(int m, int B) { return (size_t)B * (6 * m + 1 + 2 + 1 + 2); }
 KState make_kstate(const qk_krylov* k);
 // The same layout over other storage (a saved copy of d_coef and d_int).
 KState kstate_at(const qk_krylov* k, double* coef, int32_t* ints);

@@ -411,6 +411,7 @@ KState kstate_at(const qk_krylov* k, double* p, int32_t* ints) {
   s.mused = ints;
   s.status = ints + B;
   s.tau = p + (size_t)(5 * m + 3) * B;
+  s.smax = p + (size_t)(5 * m + 5) * B;
   return s;
 }
 

@@ -142,9 +142,18 @@ __device__ __forceinline__ void lanczos_b_body(VRange rg, LanczosBShared& ls,
   const bool first = rg.v0 == 0;   // the block that records the shared results
   const int j = la.j;
   const bool ro = la.reorth && j > 0;
+  // the column's scalars are fetched while the partials are in flight
+  int mused = 0;
+  double sj = 0.0, sm = 0.0;
+  if (threadIdx.x < B) {
+    mused = st.mused[threadIdx.x];
+    if (j > 0) sj = st.sigma[j * B + threadIdx.x];
+    if (ro) sm = st.sigma[(j - 1) * B + threadIdx.x];
+  }
   reduce_partials(partA, Gp, kQA, B, red, tot);
-  for (int b = threadIdx.x; b < B; b += blockDim.x) {
-    int active = st.mused[b] > j;
+  if (threadIdx.x < B) {   // B <= QK_MAX_BATCH <= blockDim
+    const int b = threadIdx.x;
+    int active = mused > j;
     if (active) {
       const double S1 = tot[b], S2 = tot[B + b];
       double alpha, c, d;
@@ -165,7 +174,6 @@ __device__ __forceinline__ void lanczos_b_body(VRange rg, LanczosBShared& ls,
           }
         }
       } else {
-        const double sj = st.sigma[j * B + b];
         alpha = sj * S1;
         c = 1.0;
         d = alpha * sj;
@@ -181,7 +189,6 @@ __device__ __forceinline__ void lanczos_b_body(VRange rg, LanczosBShared& ls,
       sc[b] = c;
       sd[b] = d;
       // component of w along v_{j-1}: <v_{j-1}, w> v_{j-1} = sigma_{j-1}^2 <u_{j-1}, w> u_{j-1}
-      const double sm = ro ? st.sigma[(j - 1) * B + b] : 0.0;
       ser[b] = sm * sm * tot[2 * B + b];
       sei[b] = sm * sm * tot[3 * B + b];
     }

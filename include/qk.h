@@ -152,9 +152,10 @@ typedef struct qk_ham qk_ham;
  * Hamiltonian of Eq. (1) on basis `b` (Sec. 3, "Hamiltonian matrix
  * construction") for `batch` field sets h_host[batch][L] (host doubles,
  * copied).  QK_MATFREE generates every row on the fly in the apply kernels;
- * for 18 <= L <= 32 it processes blocks of states sharing their high bits
- * (low-bit tables and a block list are built here; one field set or a
- * batch), otherwise one row per thread from the stored basis.  With the
+ * for 8 <= L <= 32 it processes tiles of states sharing their high bits and
+ * the particle numbers of the bits below (their tables are built here; one
+ * field set or a batch), otherwise one row per thread from the stored basis.
+ * With the
  * environment variable QK_SPLIT=1 set at this call, a single-field-set
  * Hamiltonian also builds the tables of the two-pass split (high bonds over
  * column slabs, then low bonds with the Lanczos update; vectors in a padded
@@ -191,11 +192,10 @@ qk_status qk_ham_shape(const qk_ham* H, int64_t* D, int32_t* batch, int32_t* mod
  * matrix-free modes).  For every batch item (problem k uses field set k):
  * x, y are [D][B] device arrays of `dtype`; x and y must not overlap
  * (QK_EINVAL).  QK_C128 accumulates in double, QK_C64 in float.  Matrix-free
- * Hamiltonians with 18 <= L <= 32 use the blocked kernels; a single-phase
- * vector below 4 GB is addressed with 32-bit byte offsets, a larger one
- * (the half-filled L = 32 chain) with 64-bit element offsets, which needs the
- * 11-bit block decomposition (the default there; QK_EUNSUPPORTED for another
- * one).  The same choice applies to the Lanczos H-pass of every workspace.
+ * Hamiltonians with 8 <= L <= 32 use the tiled kernels; a vector below 4 GB
+ * is addressed with 32-bit byte offsets, a larger one (the half-filled L = 32
+ * chain) with 64-bit block positions.  The same choice applies to the Lanczos
+ * H-pass of every workspace.
  */
 qk_status qk_ham_apply(const qk_ham* H, const void* x, void* y, int32_t dtype, void* stream);
 
@@ -309,20 +309,19 @@ typedef struct {
   int32_t threads;             /* threads per block of the row-streaming kernels
                                   (rounded down to batch * 2^k); 0 = 256 */
   int32_t blocks_per_cu;       /* blocks per compute unit of the row-streaming kernels; 0 = 4 */
-  int32_t blocked_wgs_per_cu;  /* work-groups per compute unit of the blocked H-pass;
+  int32_t blocked_wgs_per_cu;  /* work-groups per compute unit of the tiled H-pass;
                                   0 = as many as fit */
-  int32_t blocked_llo;         /* low bits of the block decomposition of the blocked
-                                  kernels (matrix-free, 18 <= L <= 32): 9..11 for one
-                                  phase; for batches 5..11 with the staged block of B
-                                  complex128 phases within 64 KB, the work-group's LDS
-                                  within the device limit and at most 2^20 blocks;
-                                  0 = keep */
+  int32_t blocked_llo;         /* scale of the tiles (matrix-free, 18 <= L <= 32): one
+                                  count below the default takes one bit out of every
+                                  tile.  9..11 for one phase; for batches 5..11 with a
+                                  block of B complex128 phases over that many bits
+                                  within 64 KB and at most 2^20 blocks; 0 = keep */
 } qk_launch_shape;
 
 /* Sets / reads the launch shape of a workspace's kernels.  Results do not
  * depend on the shape beyond the order of floating-point reductions.  A
  * blocked_llo that differs from the Hamiltonian's rebuilds the Hamiltonian's
- * block tables (synchronous, after all device work): every workspace and
+ * tiles (synchronous, after all device work): every workspace and
  * batch on that Hamiltonian then uses the new decomposition (batches capture
  * their graph again); no work on the Hamiltonian may be in flight on other
  * threads meanwhile.  QK_EINVAL for an unsupported low-bit count,
@@ -334,8 +333,8 @@ qk_status qk_krylov_get_shape(const qk_krylov* k, qk_launch_shape* shape);
  * Autotuner: times one step of the workspace (time step dt) for a small set
  * of launch shapes with HIP events on `stream`, on a scratch vector the call
  * allocates and frees, and applies the fastest.  With block tables the search
- * covers the low-bit count of the decomposition (three or four candidates
- * around the default) and the blocked H-pass's work-groups per CU, then the
+ * covers the scale of the tiles (three or four candidates around the default)
+ * and the tiled H-pass's work-groups per CU, then the
  * row-streaming shape.  With a non-NULL cache_path
  * the result is looked up first and stored afterwards in that JSON file,
  * keyed by (L, n_up, boundary, batch, mode, dtype, m, reorth, compute units).
@@ -371,17 +370,11 @@ qk_status qk_batch_items(const qk_batch* b, int32_t* items);
  *   1  one step of all workspaces (one graph branch each) captured into a
  *      hipGraph on first use (again when dt, P_device or a launch shape
  *      change) and replayed n_steps times;
- *   2  one persistent kernel per step that advances all workspaces, records
- *      P and advances C(t) (a work queue of every workspace's passes, each
- *      pass waiting on the previous pass of its workspace), captured into a
- *      hipGraph the same way and replayed n_steps times.  It runs the same
- *      kernel bodies on the same grids as 0 and 1, so all three give the same
- *      bits.  Requires one dtype for all workspaces, L <= 32, no split layout,
- *      reorthogonalisation 0 or 1 and 256-thread row-streaming blocks (the
- *      default shape; a batch of B items needs B a power of two), else
- *      QK_EUNSUPPORTED before anything is enqueued.  Its work queue is built
- *      on first use (device memory from the batch's allocator, kept until
- *      the batch is destroyed or a launch shape changes).
+ *   2  as 1, for batches of one dtype, L <= 32, no split layout,
+ *      reorthogonalisation 0 or 1, vectors below 4 GB and 256-thread
+ *      row-streaming blocks (the default shape; a batch of B items needs B a
+ *      power of two), else QK_EUNSUPPORTED before anything is enqueued.
+ * All three run the same kernels on the same grids and give the same bits.
  * Asynchronous.
  */
 qk_status qk_batch_run(qk_batch* b, double dt, int32_t n_steps, int32_t use_graph, double* P_device, void* stream);

@@ -373,8 +373,8 @@ def qk_batch_items(b: Batch) -> int:
 
 
 def _graph_mode(use_graph) -> int:
-    """0 (direct launches), 1 (graph of one branch per workspace) or 2 (graph of
-    the persistent step kernel); a bool means 0 or 1."""
+    """0 (direct launches), 1 (graph of one branch per workspace) or 2 (as 1, for
+    the batches that qk.h lists); a bool means 0 or 1."""
     if isinstance(use_graph, bool):
         return int(use_graph)
     m = int(use_graph)
@@ -387,7 +387,7 @@ def qk_batch_run(b: Batch, dt: float, n_steps: int, use_graph: bool | int = True
                  stream=None) -> torch.Tensor:
     """n_steps steps of every workspace; returns the device tensor P[n_steps, items].
     use_graph: 0/False direct launches, 1/True one graph branch per workspace,
-    2 the persistent step kernel (one launch per step, captured in a graph)."""
+    2 as 1 for batches of one dtype (QkError for the others, see qk.h)."""
     items = qk_batch_items(b)
     if out is None:
         out = torch.empty((n_steps, items), dtype=torch.float64, device="cuda")

@@ -286,14 +286,8 @@ QK_API qk_status qk_ham_create(const qk_basis* b, const qk_ham_params* p, const 
     }
   }
   H->llo = blocked_llo(b->L, b->N, batch, p->mode);
-  if (H->llo > 0) {
-    st = launch_blocked_build(H, s);
-    if (st != QK_OK) {
-      qk_ham_destroy(H);
-      return st;
-    }
-  }
-  st = split_build(H, s);
+  st = tile_create(H, s);
+  if (st == QK_OK) st = split_build(H, s);
   if (st != QK_OK) {
     qk_ham_destroy(H);
     return st;
@@ -322,10 +316,8 @@ QK_API qk_status qk_ham_set_fields(qk_ham* H, const double* h_host, int32_t batc
   QK_HIP(hipMemcpyAsync(H->d_fields, h_host, fbytes, hipMemcpyHostToDevice, s));
   QK_HIP(hipStreamSynchronize(s));
   H->h_host.assign(h_host, h_host + (size_t)H->basis->L * batch);
-  if (H->llo > 0) {
-    st = launch_blocked_fields(H, s);
-    if (st != QK_OK) return st;
-  }
+  st = tile_fields(H, s);
+  if (st != QK_OK) return st;
   st = split_fields(H, s);
   if (st != QK_OK) return st;
   if (H->p.mode == QK_CSR) return launch_csr_diag(H, s);
@@ -368,9 +360,7 @@ QK_API void qk_ham_destroy(qk_ham* H) {
   dev_free(H->al, H->d_rowptr);
   dev_free(H->al, H->d_cols);
   dev_free(H->al, H->d_diag);
-  dev_free(H->al, H->d_lo_state);
-  dev_free(H->al, H->d_lo_rank);
-  dev_free(H->al, H->d_blk);
+  tile_free(H);
   split_free(H);
   delete H;
 }

@@ -28,7 +28,6 @@
 #include <string>
 #include <vector>
 
-#include "qk_persist.h"
 #include "qk_step_bodies.h"
 
 namespace qk {
@@ -227,7 +226,7 @@ qk_status krylov_autotune(qk_krylov* k, double dt, const char* cache_path, hipSt
       best = sh;
     }
   };
-  const bool blocked = blocked_usable(k->H, k->dtype);
+  const bool blocked = k->H->llo > 0;
   const int llo0 = k->H->llo;
   // coordinate search: the low-bit count of the block decomposition with the
   // work-groups of the blocked H-pass first, then the shape of the
@@ -300,9 +299,6 @@ struct qk_batch {
   double* graph_P = nullptr;
   double* graph_C = nullptr;
   std::vector<uint64_t> graph_sig;  // launch configuration the graph was captured with
-  int graph_mode = 0;               // 1: one branch per workspace, 2: the persistent step kernel
-  qk::PersistPlan* plan = nullptr;  // work queue of the persistent step (mode 2)
-  std::vector<uint64_t> plan_sig;
 };
 
 namespace qk {
@@ -325,15 +321,6 @@ void batch_release(qk_batch* b) {
   if (b->graph) (void)hipGraphDestroy(b->graph);
   b->exec = nullptr;
   b->graph = nullptr;
-}
-
-static void batch_release_plan(qk_batch* b) {
-  if (b->plan) {
-    (void)hipDeviceSynchronize();   // no queued launch may still read the plan
-    persist_free(b->plan);
-  }
-  b->plan = nullptr;
-  b->plan_sig.clear();
 }
 
 qk_status batch_create(qk_krylov* const* ks, void* const* psi, const int64_t* r0, int n, qk_batch** out) {
@@ -405,7 +392,6 @@ void batch_destroy(qk_batch* b) {
   if (!b) return;
   (void)hipDeviceSynchronize();
   batch_release(b);
-  batch_release_plan(b);
   for (auto s : b->streams) (void)hipStreamDestroy(s);
   for (auto e : b->joins) (void)hipEventDestroy(e);
   if (b->fork) (void)hipEventDestroy(b->fork);
@@ -454,31 +440,32 @@ static std::vector<uint64_t> batch_signature(const qk_batch* b) {
   return sig;
 }
 
-// The persistent step's work queue for the current launch shapes (rebuilt
-// when a workspace's shape or block decomposition has changed).
-static qk_status batch_plan(qk_batch* b, const std::vector<uint64_t>& sig) {
-  if (b->plan && b->plan_sig == sig) return QK_OK;
-  batch_release(b);   // a captured graph may point at the old plan
-  batch_release_plan(b);
-  PersistInput in;
-  in.al = b->al;
-  in.ks = b->ks;
-  in.psi = b->psi;
-  in.r0 = b->r0;
-  for (void* p : b->psi0) in.psi0.push_back(p);
-  in.part = b->part;
-  in.ogrid = b->ogrid;
-  in.item_off = b->item_off;
-  qk_status st = persist_plan(in, &b->plan);
-  if (st != QK_OK) {
-    b->plan = nullptr;
-    return st;
+// What use_graph = 2 takes (qk_batch_run): one dtype, chains of at most 32
+// sites, no split layout, reorthogonalisation 0 or 1, vectors below 4 GB,
+// row-streaming blocks of 256 threads.
+static qk_status batch_mode2_check(const qk_batch* b) {
+  const char* why = nullptr;
+  for (const qk_krylov* k : b->ks) {
+    const TilePlan* tp = tile_plan(k->H, k->dtype);
+    if (k->dtype != b->ks[0]->dtype) why = "all workspaces must share one dtype";
+    else if (k->H->basis->wide) why = "chains longer than 32 sites";
+    else if (k->d_Z) why = "the two-pass split layout";
+    else if (k->reorth == 2) why = "full reorthogonalisation";
+    else if (krylov_threads(k) != kMaxBlock || block_threads(k->batch) != kMaxBlock)
+      why = "row-streaming kernels with fewer than 256 threads per block";
+    else if (k->batch == 1 && tp && tile_wide(tp)) why = "vectors of 4 GB or more";
+    if (why) break;
   }
-  b->plan_sig = sig;
-  return QK_OK;
+  if (!why) return QK_OK;
+  set_error(std::string("batched step with use_graph = 2: ") + why);
+  return QK_EUNSUPPORTED;
 }
 
 qk_status batch_run(qk_batch* b, double dt, int n_steps, int use_graph, double* P, double* C, hipStream_t s) {
+  if (use_graph == 2) {
+    const qk_status cs = batch_mode2_check(b);   // before anything is enqueued
+    if (cs != QK_OK) return cs;
+  }
   std::vector<bool> prof(b->ks.size());
   for (size_t i = 0; i < b->ks.size(); ++i) {
     prof[i] = b->ks[i]->profiling;
@@ -500,14 +487,7 @@ qk_status batch_run(qk_batch* b, double dt, int n_steps, int use_graph, double* 
     return st;
   }
   const std::vector<uint64_t> sig = batch_signature(b);
-  if (use_graph == 2) {
-    st = batch_plan(b, sig);
-    if (st != QK_OK) {
-      restore();
-      return st;
-    }
-  }
-  if (!b->exec || b->graph_mode != use_graph || b->graph_dt != dt || b->graph_P != P || b->graph_C != C ||
+  if (!b->exec || b->graph_dt != dt || b->graph_P != P || b->graph_C != C ||
       b->graph_sig != sig) {
     batch_release(b);
     hipError_t e = hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal);
@@ -515,10 +495,7 @@ qk_status batch_run(qk_batch* b, double dt, int n_steps, int use_graph, double* 
       restore();
       return hip_fail(e, "hipStreamBeginCapture");
     }
-    if (use_graph == 2)
-      st = persist_launch(b->plan, dt, P, C, b->d_counter, b->d_state, b->items, b->cap);
-    else
-      st = batch_step(b, dt, P, C, b->cap);
+    st = batch_step(b, dt, P, C, b->cap);
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(b->cap, &g);
     if (st != QK_OK || e != hipSuccess) {
@@ -533,7 +510,6 @@ qk_status batch_run(qk_batch* b, double dt, int n_steps, int use_graph, double* 
       restore();
       return hip_fail(e, "hipGraphInstantiate");
     }
-    b->graph_mode = use_graph;
     b->graph_dt = dt;
     b->graph_P = P;
     b->graph_C = C;

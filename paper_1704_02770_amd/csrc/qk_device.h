@@ -177,10 +177,7 @@ __device__ __forceinline__ typename Cx<T>::V h_row(uint32_t r, int b, const Mode
   return acc;
 }
 
-// The block index and block count a kernel body works with.  A plain launch
-// passes (blockIdx.x, gridDim.x); the persistent step kernel (qk_persist.hip)
-// passes the tile it has claimed and the tile count of that pass, so a body
-// produces the same values, partial sums included, either way.
+// The block index and block count a kernel body works with.
 struct VGrid {
   uint32_t id, n;
 };
@@ -430,9 +427,9 @@ __device__ __forceinline__ void lanczos_h_scalars(int B, const KState& st, const
 }
 
 
-qk_status launch_blocked_lanczos_h(const qk_ham* H, int dtype, const void* uj, const void* ujm1, void* w,
-                                   const KState& st, const LanczosArgs& la, const double* partB, int Gp,
-                                   double* partA, int* grid_out, int wgs_per_cu, hipStream_t s);
+qk_status launch_tile_lanczos_h(const TilePlan& P, int dtype, const void* uj, const void* ujm1, void* w,
+                                const KState& st, const LanczosArgs& la, const double* partB, int Gp, double* partA,
+                                int* grid_out, int wgs, hipStream_t s);
 
 // Two-pass split iteration (qk_split.hip): the pre-pass partials |x|^2 and
 // Re<x, H_lo x> of a step's initial vector, the high pass

@@ -81,6 +81,10 @@ hipError_t dev_alloc_async(const qk_allocator& a, void** p, size_t bytes, hipStr
 hipError_t dev_free_async(const qk_allocator& a, void* p, hipStream_t s);
 }  // namespace qk
 
+namespace qk {
+struct TilePlan;
+}  // namespace qk
+
 struct qk_basis {
   qk_allocator al;
   int32_t L = 0, N = 0;
@@ -104,13 +108,10 @@ struct qk_ham {
   uint32_t* d_cols = nullptr;     // [nnz]
   double* d_diag = nullptr;       // [D][batch]
   int64_t nnz = 0;
-  // blocked matrix-free form (llo > 0): low-bit tables and the block list
-  int llo = 0;
-  uint16_t* d_lo_state = nullptr; // [2^llo]
-  uint16_t* d_lo_rank = nullptr;  // [2^llo]
-  void* d_blk = nullptr;          // [nblk] block entries (high bits, first row, ring-partner first row)
-  int nblk = 0;
-  uint64_t tables_gen = 0;        // incremented whenever the block tables are rebuilt
+  // tiled matrix-free form (qk_tile.hip), one plan per element size: complex64, complex128
+  qk::TilePlan* tile[2] = {nullptr, nullptr};
+  int llo = 0;                    // low bits of its block decomposition (blocked_llo)
+  uint64_t tables_gen = 0;        // incremented whenever the tiles are rebuilt
   // two-pass high/low split (one field set, 18 <= L <= 32): tables of qk_split.hip
   void* split = nullptr;
 };
@@ -124,7 +125,7 @@ struct qk_krylov {
   // launch shape (qk_krylov_set_shape / qk_krylov_autotune); 0 = default
   int threads = 0;                // threads per block of the row-streaming kernels (B * 2^k, <= 256)
   int blocks_per_cu = 0;          // blocks per CU of the row-streaming kernels
-  int blocked_wgs = 0;            // work-groups per CU of the blocked H-pass
+  int blocked_wgs = 0;            // work-groups per CU of the tiled H-pass
   int grid = 0;                   // blocks of the streaming kernels (multiple of 8)
   void* d_U = nullptr;            // m slots of ustride elements: u_1..u_m
   uint64_t ustride = 0;           // elements per slot: D * batch, or the padded length of the split layout
@@ -184,12 +185,15 @@ qk_status launch_csr_build(qk_ham* H, hipStream_t s);
 qk_status launch_csr_diag(qk_ham* H, hipStream_t s);
 qk_status launch_ham_apply(const qk_ham* H, const void* x, void* y, int dtype, hipStream_t s);
 int blocked_llo(int L, int N, int B, int mode);
-qk_status launch_blocked_build(qk_ham* H, hipStream_t s);
-qk_status launch_blocked_apply(const qk_ham* H, const void* x, void* y, int dtype, hipStream_t s);
-qk_status launch_blocked_fields(qk_ham* H, hipStream_t s);
-bool blocked_usable(const qk_ham* H, int dtype);
+// tiled matrix-free form (qk_tile.hip)
+qk_status tile_create(qk_ham* H, hipStream_t s);   // no-op for Hamiltonians it does not cover
+void tile_free(qk_ham* H);
+qk_status tile_fields(const qk_ham* H, hipStream_t s);   // after a change of the fields
+const TilePlan* tile_plan(const qk_ham* H, int dtype);   // NULL: not covered
+bool tile_wide(const TilePlan* P);   // vectors that 32-bit byte offsets do not reach
+qk_status launch_tile_apply(const TilePlan& P, int dtype, const void* x, void* y, hipStream_t s);
 // Valid low-bit counts of the block decomposition for this Hamiltonian
-// (empty without block tables), and a rebuild of the tables at another one.
+// (empty without one), and a rebuild of the tiles at another one.
 bool blocked_llo_valid(const qk_ham* H, int llo);
 qk_status blocked_rebuild(qk_ham* H, int llo);
 // two-pass high/low split (qk_split.hip)

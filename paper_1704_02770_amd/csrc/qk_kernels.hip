@@ -512,7 +512,7 @@ static void launch_apply_rows(const qk_ham* H, const void* x, void* y, hipStream
 
 qk_status launch_ham_apply(const qk_ham* H, const void* x, void* y, int dtype, hipStream_t s) {
   if (split_usable(H) && H->batch == 1) return launch_split_apply(H, x, y, dtype, s);
-  if (blocked_usable(H, dtype)) return launch_blocked_apply(H, x, y, dtype, s);
+  if (const TilePlan* tp = tile_plan(H, dtype)) return launch_tile_apply(*tp, dtype, x, y, s);
   const bool wide = H->basis->wide;
   if (dtype == QK_C128) {
     if (wide) launch_apply_rows<double, uint64_t>(H, x, y, s);
@@ -631,9 +631,9 @@ static qk_status krylov_step_t(qk_krylov* k, void* psi_v, double dt, hipStream_t
     V* w = U + (size_t)j * stride;
     QK_MARK(QK_KERNEL_LANCZOS_H, true);
     int Ga = G;
-    if (blocked_usable(H, k->dtype)) {
-      qk_status bs = launch_blocked_lanczos_h(H, k->dtype, uj, ujm1, w, st, la, pB, GB, k->d_partA, &Ga,
-                                              k->blocked_wgs, s);
+    if (const TilePlan* tp = tile_plan(H, k->dtype)) {
+      qk_status bs = launch_tile_lanczos_h(*tp, k->dtype, uj, ujm1, w, st, la, pB, GB, k->d_partA, &Ga,
+                                           k->blocked_wgs, s);
       if (bs != QK_OK) return bs;
     } else if (H->basis->wide) {
       launch_lanczos_rows<T, uint64_t>(H, uj, ujm1, w, st, la, pB, GB, G, threads, k->d_partA, s);

@@ -1,9 +1,7 @@
-// Kernel bodies of one Krylov step besides the blocked H-pass (Sec. 2
-// "Krylov subspace methods"; rows of Eq. (1); the survival probability of
-// Sec. 4): the row-form H-pass, the partial-sum totals, the update pass, the
-// projected exponential, the combination and the overlap, as device functions
-// over a virtual grid (VGrid), so that the plain launches of qk_kernels.hip
-// and the persistent step kernel of qk_persist.hip run the same code.
+// Kernel bodies of one Krylov step besides the tiled H-pass (Sec. 2 "Krylov
+// subspace methods"; rows of Eq. (1); the survival probability of Sec. 4): the
+// row-form H-pass, the partial-sum totals, the update pass, the projected
+// exponential, the combination and the overlap.
 #pragma once
 
 #include "qk_device.h"

@@ -4,6 +4,7 @@
 // failures into QK_EHIP with the runtime's message in qk_last_error().
 #include <algorithm>
 #include <cmath>
+#include <cstdlib>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -397,15 +398,28 @@ qk_status qk::krylov_create(const qk_ham* H, int32_t m, int32_t dtype, int32_t r
   k->ustride = use_split ? split_padded_len(H, dtype) : (uint64_t)k->D * k->batch;
   const size_t vec = elem_bytes(dtype) * (size_t)k->ustride;
   k->al = al;
+  // the coefficients' allocation also holds the control words (cleared with
+  // them) and exchange vectors of the resident recurrence
+  const auto pad = [](size_t n) { return (n + 255) & ~(size_t)255; };
+  size_t head = 0, body = 0;
+  if (!use_split) resident_bytes(k, &head, &body);
+  const size_t coef = pad(sizeof(double) * kstate_doubles(m, k->batch)), ctl = pad(head);
   hipError_t e = dev_alloc(k->al, &k->d_U, vec * (size_t)m);
   if (e == hipSuccess)
     e = dev_alloc(k->al, (void**)&k->d_partA, sizeof(double) * (size_t)kMaxPartialBlocks * kQA * k->batch);
   if (e == hipSuccess) e = dev_alloc(k->al, (void**)&k->d_partB, sizeof(double) * (size_t)kMaxPartialBlocks * k->batch);
-  if (e == hipSuccess) e = dev_alloc(k->al, (void**)&k->d_coef, sizeof(double) * kstate_doubles(m, k->batch));
+  if (e == hipSuccess) e = dev_alloc(k->al, (void**)&k->d_coef, coef + ctl + body);
   if (e == hipSuccess) e = dev_alloc(k->al, (void**)&k->d_int, sizeof(int32_t) * 2 * k->batch);
   if (e == hipSuccess) e = dev_alloc(k->al, (void**)&k->d_ptot, sizeof(double) * (size_t)(kQA + 1) * k->batch);
-  if (e == hipSuccess) e = hipMemset(k->d_coef, 0, sizeof(double) * kstate_doubles(m, k->batch));
+  if (e == hipSuccess) e = hipMemset(k->d_coef, 0, coef + ctl);
   if (e == hipSuccess) e = hipMemset(k->d_int, 0, sizeof(int32_t) * 2 * k->batch);
+  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);   // any stream may use the workspace at once
+  if (e == hipSuccess && head) {
+    k->d_res = (char*)k->d_coef + coef;
+    k->d_X = (char*)k->d_res + ctl;
+    // QK_RESIDENT_JOIN=n, read here: only n work-groups register
+    if (const char* ev = getenv("QK_RESIDENT_JOIN")) k->res_join = std::max(0, atoi(ev));
+  }
   if (e == hipSuccess && reorth == 2) {
     const size_t chunks = (size_t)(m + kReorthChunk - 1) / kReorthChunk;
     e = dev_alloc(k->al, (void**)&k->d_rpart, sizeof(double) * chunks * kReorthGrid * 2 * kReorthChunk * k->batch);

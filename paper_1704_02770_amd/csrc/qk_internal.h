@@ -139,6 +139,9 @@ struct qk_krylov {
   // two-pass split iteration (one field set, no reorthogonalisation)
   void* d_Z = nullptr;            // [ustride] high-pass result z of the current iteration (padded layout)
   double* d_sp = nullptr;         // partial sums: high pass [kMaxPartialBlocks][2], low pass 2 x ([kMaxPartialBlocks] norms, [kMaxPartialBlocks] forms)
+  void* d_res = nullptr;          // resident recurrence of small sectors (qk_resident.hip): control words
+  void* d_X = nullptr;            // and its two exchange vectors (both in the coefficients' allocation)
+  int res_join = 0;               // work-groups that may register there (0: all)
   // event timing (qk_krylov_profile)
   bool profiling = false;
   struct Pending { int kind; hipEvent_t start, end; };
@@ -196,6 +199,12 @@ qk_status launch_tile_apply(const TilePlan& P, int dtype, const void* x, void* y
 // (empty without one), and a rebuild of the tiles at another one.
 bool blocked_llo_valid(const qk_ham* H, int llo);
 qk_status blocked_rebuild(qk_ham* H, int llo);
+// resident recurrence of small sectors (qk_resident.hip): the whole Lanczos
+// recurrence of a step in one launch; |u_m|^2 per column in d_partB
+// Bytes of its control words (cleared at the start) and exchange vectors; 0 for
+// workspaces it does not cover.
+void resident_bytes(const qk_krylov* k, size_t* head, size_t* body);
+qk_status launch_resident(qk_krylov* k, void* psi, double rtol, hipStream_t s);
 // two-pass high/low split (qk_split.hip)
 qk_status split_build(qk_ham* H, hipStream_t s);   // no-op unless QK_SPLIT=1, one field set, matrix-free, 18 <= L <= 30
 qk_status split_fields(qk_ham* H, hipStream_t s);
@@ -212,8 +221,9 @@ qk_status krylov_create(const qk_ham* H, int32_t m, int32_t dtype, int32_t reort
 // How far one Krylov step goes: the basis and Lanczos coefficients only, or
 // the whole step with psi replaced by the combination.
 enum class StepUpTo { basis, combination };
+// beside: steps of other workspaces run on other streams at the same time.
 qk_status launch_krylov_step(qk_krylov* k, void* psi, double dt, hipStream_t s,
-                             StepUpTo upto = StepUpTo::combination);
+                             StepUpTo upto = StepUpTo::combination, bool beside = false);
 // One step of at most tau_max whose length the device chooses from the error
 // estimate: st.tau[b] receives the accepted step of column b, st.tau[B + b] a
 // suggested next step; every column advances by the smallest accepted step.

@@ -21,18 +21,23 @@
 namespace qk {
 
 // C(n, k) for n, k < K by Pascal's rule, saturated at 2^32 - 1 (entries that
-// large are never used: every term of a rank is below D < 2^32).
+// large are never used: every term of a rank is below D < 2^32).  Row by row,
+// a thread per entry, the rows in LDS (one thread on memory took 81 us, all of
+// a small sector's build).
 template <int K>
-__global__ void k_binom_table(uint32_t* tab) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  for (int n = 0; n < K; ++n)
-    for (int k = 0; k < K; ++k) {
-      uint64_t v;
-      if (k > n) v = 0;
-      else if (k == 0 || k == n) v = 1;
-      else v = (uint64_t)tab[(n - 1) * K + k - 1] + tab[(n - 1) * K + k];
-      tab[n * K + k] = v > 0xffffffffull ? 0xffffffffu : (uint32_t)v;
+__global__ void __launch_bounds__(128) k_binom_table(uint32_t* tab) {
+  __shared__ uint32_t row[2][K + 1];
+  const int k = threadIdx.x;
+  for (int n = 0; n < K; ++n) {
+    uint32_t* cur = row[n & 1];
+    const uint32_t* up = row[(n & 1) ^ 1];
+    if (k < K) {
+      const uint64_t v = k > n ? 0 : (k == 0 || k == n) ? 1 : (uint64_t)up[k - 1] + up[k];
+      cur[k] = v > 0xffffffffull ? 0xffffffffu : (uint32_t)v;
+      tab[n * K + k] = cur[k];
     }
+    __syncthreads();
+  }
 }
 
 constexpr int kBasisChunk = 8;
@@ -421,12 +426,12 @@ qk_status launch_basis_build(qk_basis* b, hipStream_t s) {
   const uint64_t per = (uint64_t)kBasisThreads * kBasisChunk;
   const uint64_t blocks = ((uint64_t)b->D + per - 1) / per;
   if (b->wide) {
-    hipLaunchKernelGGL(k_binom_table<StateT<uint64_t>::kStride>, dim3(1), dim3(1), 0, s, b->d_binom);
+    hipLaunchKernelGGL(k_binom_table<StateT<uint64_t>::kStride>, dim3(1), dim3(128), 0, s, b->d_binom);
     QK_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_basis_build<uint64_t>, dim3((unsigned)blocks), dim3(kBasisThreads), 0, s,
                        (uint64_t*)b->d_states, (uint32_t)b->D, b->L, b->N, b->d_binom);
   } else {
-    hipLaunchKernelGGL(k_binom_table<StateT<uint32_t>::kStride>, dim3(1), dim3(1), 0, s, b->d_binom);
+    hipLaunchKernelGGL(k_binom_table<StateT<uint32_t>::kStride>, dim3(1), dim3(128), 0, s, b->d_binom);
     QK_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_basis_build<uint32_t>, dim3((unsigned)blocks), dim3(kBasisThreads), 0, s,
                        (uint32_t*)b->d_states, (uint32_t)b->D, b->L, b->N, b->d_binom);
@@ -565,7 +570,7 @@ static void launch_combine(typename Cx<T>::V* psi, const typename Cx<T>::V* U, u
 
 template <typename T>
 static qk_status krylov_step_t(qk_krylov* k, void* psi_v, double dt, hipStream_t s, StepUpTo upto,
-                               const AdaptiveStep* ad = nullptr) {
+                               bool beside = false, const AdaptiveStep* ad = nullptr) {
   using V = typename Cx<T>::V;
   const qk_ham* H = k->H;
   const int B = H->batch, threads = krylov_threads(k), G = k->grid, m = k->m;
@@ -624,7 +629,19 @@ static qk_status krylov_step_t(qk_krylov* k, void* psi_v, double dt, hipStream_t
     pB = spB[m & 1];
     GB = Glo;
   }
-  for (int j = 0; j < (k->d_Z ? 0 : m); ++j) {
+  // small sectors: one launch for the whole recurrence; kernel by kernel while
+  // they are being timed, and beside other workspaces' steps, whose kernels
+  // fill the compute units that its work-groups would wait for (64 phases of
+  // the 20-site ring with single rings of 16, 18 and 22 sites: 15.2 ms with
+  // it, 14.7 ms without)
+  const bool resident = k->d_res && !k->profiling && !beside;
+  if (resident) {
+    qk_status rs = launch_resident(k, psi, rtol, s);
+    if (rs != QK_OK) return rs;
+    pB = k->d_partB;
+    GB = 1;
+  }
+  for (int j = 0; j < (k->d_Z || resident ? 0 : m); ++j) {
     LanczosArgs la{j, m, rtol, k->reorth == 1 ? 1 : 0};
     const V* uj = j == 0 ? psi : U + (size_t)(j - 1) * stride;
     const V* ujm1 = j == 0 ? nullptr : (j == 1 ? psi : U + (size_t)(j - 2) * stride);
@@ -749,15 +766,15 @@ qk_status profile_collect(qk_krylov* k) {
   return QK_OK;
 }
 
-qk_status launch_krylov_step(qk_krylov* k, void* psi, double dt, hipStream_t s, StepUpTo upto) {
-  if (k->dtype == QK_C128) return krylov_step_t<double>(k, psi, dt, s, upto);
-  return krylov_step_t<float>(k, psi, dt, s, upto);
+qk_status launch_krylov_step(qk_krylov* k, void* psi, double dt, hipStream_t s, StepUpTo upto, bool beside) {
+  if (k->dtype == QK_C128) return krylov_step_t<double>(k, psi, dt, s, upto, beside);
+  return krylov_step_t<float>(k, psi, dt, s, upto, beside);
 }
 
 qk_status launch_krylov_adaptive_step(qk_krylov* k, void* psi, double tau_max, double tol, hipStream_t s) {
   const AdaptiveStep ad{tau_max, tol};
-  if (k->dtype == QK_C128) return krylov_step_t<double>(k, psi, tau_max, s, StepUpTo::combination, &ad);
-  return krylov_step_t<float>(k, psi, tau_max, s, StepUpTo::combination, &ad);
+  if (k->dtype == QK_C128) return krylov_step_t<double>(k, psi, tau_max, s, StepUpTo::combination, false, &ad);
+  return krylov_step_t<float>(k, psi, tau_max, s, StepUpTo::combination, false, &ad);
 }
 
 qk_status launch_return_prob(const qk_basis* b, int64_t r0, const void* psi0, const void* psi, int dtype, int B,

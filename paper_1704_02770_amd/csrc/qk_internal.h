@@ -204,7 +204,6 @@ qk_status blocked_rebuild(qk_ham* H, int llo);
 // Bytes of its control words (cleared at the start) and exchange vectors; 0 for
 // workspaces it does not cover.
 void resident_bytes(const qk_krylov* k, size_t* head, size_t* body);
-qk_status launch_resident(qk_krylov* k, void* psi, double rtol, hipStream_t s);
 // two-pass high/low split (qk_split.hip)
 qk_status split_build(qk_ham* H, hipStream_t s);   // no-op unless QK_SPLIT=1, one field set, matrix-free, 18 <= L <= 30
 qk_status split_fields(qk_ham* H, hipStream_t s);
@@ -221,6 +220,15 @@ qk_status krylov_create(const qk_ham* H, int32_t m, int32_t dtype, int32_t reort
 // How far one Krylov step goes: the basis and Lanczos coefficients only, or
 // the whole step with psi replaced by the combination.
 enum class StepUpTo { basis, combination };
+struct AdaptiveStep {
+  double tau_max, tol;
+};
+// The whole step in one launch, for a workspace that it covers at present; ad != NULL: an
+// adaptive step of at most tau.  Where *done is false, the exponential and the
+// combination are left to the passes' kernels (|u_m|^2 in d_partB).
+bool resident_covers(const qk_krylov* k);
+qk_status launch_resident(qk_krylov* k, void* psi, double rtol, double tau, StepUpTo upto, const AdaptiveStep* ad,
+                          hipStream_t s, bool* done);
 // beside: steps of other workspaces run on other streams at the same time.
 qk_status launch_krylov_step(qk_krylov* k, void* psi, double dt, hipStream_t s,
                              StepUpTo upto = StepUpTo::combination, bool beside = false);

@@ -220,15 +220,9 @@ k_small_expm(KState st, int m, int B, double tau, const double* __restrict__ tau
 }
 
 
-// Step-size control of one adaptive step (the rule of Expokit, which the
-// paper's runs use through SLEPc): starting from tau_max, the step tau of
-// column b is accepted when the estimate err(tau) = ||psi|| beta_m
-// |[exp(-i tau T)]_{m,1}| is at most 1.2 tau tol, and otherwise replaced by
-// 0.9 tau (tau tol / err)^(1 / (m - 1)), kept within [tau / 10, 0.9 tau].  The
-// Krylov basis does not depend on tau, so only the small exponential is
-// recomputed.  A recurrence that stopped early spans an invariant subspace
-// and accepts tau_max.  st.tau[b] = accepted step, st.tau[B + b] = suggested
-// next step (0.9 tau (tau tol / err)^(1/(m-1)), at most 10 tau).
+// Step size of column b by one wave: st.tau[b] = accepted step, st.tau[B + b] =
+// suggested next step.  A recurrence that stopped early spans an invariant
+// subspace and accepts tau_max.
 __global__ void __launch_bounds__(64)
 k_step_size(KState st, int m, int B, double tau_max, double tol, const double* __restrict__ partB, int Gp) {
   const int b = blockIdx.x;
@@ -236,24 +230,8 @@ k_step_size(KState st, int m, int B, double tau_max, double tol, const double* _
   const double beta_last = last_residual_norm(partB, Gp, B, b, i);
   const int mu = st.mused[b];
   double tau = tau_max, next = tau_max;
-  if (st.status[b] == QK_OK && mu == m && m > 1) {
-    const TriLane t = tri_lane(st, B, b, mu, i);
-    const double n0 = st.n0[b];
-    const double xm = 1.0 / (double)(m - 1);
-    double err = 0.0;
-    for (int it = 0; it < 60; ++it) {
-      double er, ei;
-      tri_expm_e1(t.al, t.be, t.bl, t.on, i, tau, er, ei);
-      err = n0 * beta_last * __shfl(sqrt(er * er + ei * ei), mu - 1);
-      if (err <= 1.2 * tau * tol) break;
-      double nt = 0.9 * tau * pow(tau * tol / err, xm);
-      if (!(nt >= 0.1 * tau)) nt = 0.1 * tau;   // also catches a NaN estimate
-      if (nt > 0.9 * tau) nt = 0.9 * tau;
-      tau = nt;
-    }
-    next = (err > 0.0) ? 0.9 * tau * pow(tau * tol / err, xm) : 10.0 * tau;
-    if (!(next <= 10.0 * tau)) next = 10.0 * tau;
-  }
+  if (st.status[b] == QK_OK && mu == m && m > 1)
+    tau = step_size(tri_lane(st, B, b, mu, i), m, i, st.n0[b] * beta_last, tau_max, tol, next);
   if (i == 0) {
     st.tau[b] = tau;
     st.tau[B + b] = next;
@@ -548,10 +526,6 @@ static void launch_lanczos_rows(const qk_ham* H, const typename Cx<T>::V* uj, co
                        H->basis->d_binom, H->d_fields, st, la, partB, Gp, partA);
 }
 
-struct AdaptiveStep {
-  double tau_max, tol;
-};
-
 template <typename T, bool NT>
 static void launch_combine(typename Cx<T>::V* psi, const typename Cx<T>::V* U, uint32_t D, int B, int m,
                            const KState& st, bool pack2, int G, int threads, size_t cfb, hipStream_t s) {
@@ -629,15 +603,16 @@ static qk_status krylov_step_t(qk_krylov* k, void* psi_v, double dt, hipStream_t
     pB = spB[m & 1];
     GB = Glo;
   }
-  // small sectors: one launch for the whole recurrence; kernel by kernel while
+  // small sectors: one launch for the whole step; kernel by kernel while
   // they are being timed, and beside other workspaces' steps, whose kernels
   // fill the compute units that its work-groups would wait for (64 phases of
   // the 20-site ring with single rings of 16, 18 and 22 sites: 15.2 ms with
   // it, 14.7 ms without)
-  const bool resident = k->d_res && !k->profiling && !beside;
+  const bool resident = resident_covers(k) && !k->profiling && !beside;
   if (resident) {
-    qk_status rs = launch_resident(k, psi, rtol, s);
-    if (rs != QK_OK) return rs;
+    bool done = false;
+    const qk_status rs = launch_resident(k, psi, rtol, ad ? ad->tau_max : dt, upto, ad, s, &done);
+    if (rs != QK_OK || done) return rs;
     pB = k->d_partB;
     GB = 1;
   }

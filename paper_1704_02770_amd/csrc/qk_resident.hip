@@ -1,5 +1,5 @@
-// One launch for the whole Lanczos recurrence of a small sector (Sec. 2
-// "Krylov subspace methods"), with a row per thread.
+// One launch for a whole Krylov step of a small sector (Sec. 2 "Krylov subspace
+// methods"), with a row per thread.
 //
 // Below about 200,000 elements a Krylov step is a chain of 2 m short kernels:
 // each starts by fetching what the previous one left in memory and ends by
@@ -11,7 +11,8 @@
 //      every thread reads w at its neighbours and forms u_{j+1} there as well
 //      as on its own row, the same expression in both places, so the same bits;
 //   B  |u_{j+1}|^2 is totalled (beta_j); no vector is exchanged.
-// u_{j+1} goes to the basis slot for the combination that follows.
+// u_{j+1} goes to the basis slot.  At the end every work-group computes the
+// small exponential for itself and combines its own rows of the basis.
 //
 // Totals and waiting are one thing: a work-group publishes its partial sums as
 // 8-byte words that hold 32 bits of the value and the number of the exchange,
@@ -30,15 +31,21 @@
 // in memory: slower, the same arithmetic, and no wait for a work-group that
 // may never run beside them.
 //
-// What bounds it: the two exchanges of an iteration, 3.0 us at 924 rows and
-// 8 us at 184,756 (a store to the agent's point of coherence and the read that
-// sees it are about 0.7 us each, the rest is the sum over a work-group and the
-// neighbours' 20 gathers).  A step of 30 vectors, complex128, one phase, against
-// the passes: L = 12 (open, m = 20) 105 against 244 us, L = 16 184 against 420,
-// L = 18 237, L = 20 329 against 690.
+// Sectors of up to 1,024 rows (over all columns) take one work-group, which
+// keeps u_j in LDS and exchanges nothing (k_resident_one).
+//
+// What bounds it: the two exchanges of an iteration, 1.4 to 3 us for the first
+// (all must have stored w) and 1.1 us for the second, a load that sees another
+// work-group's store taking 0.7 us; the neighbours, 1.0 to 1.3 us (3 us at
+// L = 20); three barriers and the scalars between them, 1.5 us.  In one
+// work-group 1.4 us an iteration, the gathers from LDS and the sums over the
+// waves.  A step of 30 vectors, complex128, one phase, against the passes:
+// L = 12 (open, 20 vectors) 51 against 244 us, L = 16 171 against 420, L = 18
+// 217, L = 20 325 against 690; of four phases at L = 12 in complex64 182.
 #include <algorithm>
 #include <type_traits>
 
+#include "qk_step_bodies.h"
 #include "qk_tile.h"
 
 namespace qk {
@@ -58,10 +65,12 @@ struct ResCtl {
   uint64_t joined;    // number of the launch's first exchange << 32 | registered work-groups
 };
 constexpr uint32_t kClosed = 0x80000000u;
+enum { kTailNone = 0, kTailStep = 1, kTailAdaptive = 2 };
 
 struct ResArgs {
-  int L, pbc, B, lbp, m, olo, nbonds;
+  int L, pbc, B, lbp, m, nbonds;
   uint32_t D;
+  int groups;                      // work-groups that the rows take
   int join_max;                    // work-groups that may register (all of them, or fewer in tests)
   double half_jxy, jz, rtol;
   const uint32_t* states;
@@ -70,11 +79,12 @@ struct ResArgs {
   uint64_t stride;                 // elements of a basis slot
   uint64_t* words;                 // [2][groups][2][lanes per row] pairs of words
   ResCtl* ctl;
+  int tail;                        // what follows the recurrence (kTail*)
   double* norm2;                   // [B] |u_m|^2
+  double tau, tol;                 // the step, or the largest one and the tolerance of an adaptive step
 };
 
 constexpr int kSc1 = 16;   // agent scope
-constexpr int kResLoads = 7;
 
 template <typename V>
 struct ResBuf {
@@ -114,6 +124,10 @@ struct ResShared {
   double red[2 * kResMaxThreads / 64 * kResMaxLanes];
   double sa[kResMaxLanes], sb[kResMaxLanes], sc[kResMaxLanes], sd[kResMaxLanes];
   int act[kResMaxLanes];
+  // per column: coefficients and scales, then the combination's coefficients in al and be
+  double al[kResMaxLanes * 64], be[kResMaxLanes * 64], sg[kResMaxLanes * 64];
+  double n0[kResMaxLanes], last[kResMaxLanes];   // |psi|, |u_m|
+  int mu[kResMaxLanes], ok[kResMaxLanes];
   uint32_t tab[kBinomStride * kBinomStride];
   uint32_t ticket, joined, epoch, dead, go;
 };
@@ -216,36 +230,39 @@ __device__ __forceinline__ double res_collect(ResShared& sh, const ResArgs& ra, 
   return res_wave_sum(acc, cols);
 }
 
-// The sum over a row's hops, bond by bond in ascending order with the ring bond
-// last, x zero for an inactive bond, in the order that the pass's plain kernels
-// use (TileArgs::order): complex64 gives the same bits as they do.
-// BLOCKED: that of a block decomposition (complex64 from 18 sites on);
-// otherwise one by one.  flush: bit k set where the hop on bond k ends a group
-// of four.
-template <typename T, bool BLOCKED>
+// The sum over a row's hops, slot by slot, x zero where there is none, in the
+// order that the pass's plain kernels use (TileArgs::order): complex64 gives
+// the same bits as they do.
+// OLO = 0: one by one; slot k is bond k.
+// OLO > 0: that of a block decomposition (complex64 from 18 sites on) -- bonds
+// below OLO - 1 one by one (slot k is bond k), the active ones of the bonds
+// from OLO on in groups of four (the next slots in turn, so that a group ends
+// at the same slot in every lane), and bond OLO - 1 with the ring bond (the
+// last two slots).
+template <typename T, int KMAX, int OLO>
 struct HopSum {
   using V = typename Cx<T>::V;
   V hs = {0, 0}, ac = {0, 0}, vd = {0, 0}, vw = {0, 0};
-  __device__ __forceinline__ void add(const ResArgs& ra, int k, V x, uint32_t flush) {
-    if (!BLOCKED || k < ra.olo - 1) {
+  __device__ __forceinline__ void add(int k, V x) {
+    if (OLO == 0 || k < OLO - 1) {
       hs.x += x.x;
       hs.y += x.y;
-    } else if (k == ra.L - 1) {
+    } else if (k == KMAX - 1) {
       vw = x;
-    } else if (k == ra.olo - 1) {
+    } else if (k == KMAX - 2) {
       vd = x;
     } else {
       ac.x += x.x;
       ac.y += x.y;
-      const bool f = ((flush >> k) & 1u) != 0u;
-      hs.x += f ? ac.x : (T)0;
-      hs.y += f ? ac.y : (T)0;
-      ac.x = f ? (T)0 : ac.x;
-      ac.y = f ? (T)0 : ac.y;
+      if (((k - (OLO - 1)) & 3) == 3) {
+        hs.x += ac.x;
+        hs.y += ac.y;
+        ac.x = ac.y = (T)0;
+      }
     }
   }
   __device__ __forceinline__ V total() const {
-    if (!BLOCKED) return hs;
+    if (OLO == 0) return hs;
     V t = {hs.x + ac.x, hs.y + ac.y};
     t.x += vd.x + vw.x;
     t.y += vd.y + vw.y;
@@ -253,11 +270,47 @@ struct HopSum {
   }
 };
 
-template <typename T, bool BLOCKED>
+// Rows of the sector as a thread sees them.
+struct ResRows {
+  const ResArgs& ra;
+  const uint32_t* tab;   // binomials, in LDS
+  int p;                 // column
+  uint32_t size;         // bytes of an element
+  // the partner of state s (row r) across bond k, kNoRow if the bond's bits
+  // agree; pc: set bits below k
+  __device__ __forceinline__ uint32_t partner(uint32_t s, uint32_t r, int k, int pc) const {
+    uint32_t q;
+    if (k < ra.L - 1) {
+      const uint32_t b0 = (s >> k) & 1u;
+      const uint32_t c = tab[k * kBinomStride + pc];
+      if (b0 == ((s >> (k + 1)) & 1u)) return kNoRow;
+      q = b0 ? r + c : r - c;
+    } else {
+      if (((s ^ (s >> (ra.L - 1))) & 1u) == 0u) return kNoRow;
+      q = cns_rank<uint32_t>(s ^ (1u | (1u << (ra.L - 1))), tab);
+    }
+    return (q * (uint32_t)ra.B + p) * size;
+  }
+  // offsets of the neighbours by slot (HopSum), kNoRow where there is none:
+  // slot k at lo[k * pitch], in LDS, this thread's own
+  template <int KMAX, int OLO>
+  __device__ __forceinline__ void slots(uint32_t s, uint32_t r, uint32_t* lo, int pitch) const {
+    for (int k = 0; k < KMAX; ++k) lo[k * pitch] = kNoRow;
+    int pc = 0, n = OLO - 1;
+    for (int k = 0; k < ra.nbonds; ++k) {
+      const uint32_t o = partner(s, r, k, pc);
+      pc += (int)((s >> k) & 1u);
+      if (o == kNoRow) continue;
+      lo[(OLO == 0 || k < OLO - 1 ? k : k == OLO - 1 ? KMAX - 2 : k == ra.L - 1 ? KMAX - 1 : n++) * pitch] = o;
+    }
+  }
+};
+
+template <typename T, int OLO>
 __device__ __forceinline__ typename Cx<T>::V res_w(double d, T g, T ca, T cb,
                                                    typename Cx<T>::V u, typename Cx<T>::V um, typename Cx<T>::V hs) {
   typename Cx<T>::V h, w;
-  if (!BLOCKED) {
+  if (OLO == 0) {
     const T dd = (T)d;
     h.x = dd * u.x;
     h.y = dd * u.y;
@@ -274,6 +327,84 @@ __device__ __forceinline__ typename Cx<T>::V res_w(double d, T g, T ca, T cb,
     w.y = ca * h.y - cb * um.y;
   }
   return w;
+}
+
+// After the recurrence: every work-group computes the step's length and the
+// combination's coefficients of all columns for itself, a wave a column (the
+// values are the same in all of them).
+__device__ __forceinline__ void res_coefs(ResShared& sh, const ResArgs& ra, const KState& st, bool first) {
+  const int B = ra.B, m = ra.m, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = (int)blockDim.x >> 6;
+  auto tri = [&](int b, int mu) {
+    TriLane t;
+    t.on = lane < mu;
+    t.al = t.on ? sh.al[b * 64 + lane] : 0.0;
+    t.be = lane + 1 < mu ? sh.be[b * 64 + lane] : 0.0;
+    t.bl = t.on && lane > 0 ? sh.be[b * 64 + lane - 1] : 0.0;
+    return t;
+  };
+  double tau = ra.tau;
+  if (ra.tail == kTailAdaptive) {
+    for (int b = wave; b < B; b += waves) {
+      double next = ra.tau, own = ra.tau;
+      if (sh.ok[b] && sh.mu[b] == m && m > 1) own = step_size(tri(b, m), m, lane, sh.n0[b] * sh.last[b], ra.tau, ra.tol, next);
+      if (lane == 0) {
+        sh.sa[b] = own;
+        if (first) {
+          st.tau[b] = own;
+          st.tau[B + b] = next;
+        }
+      }
+    }
+    __syncthreads();
+    tau = sh.sa[0];
+    for (int c = 1; c < B; ++c) tau = fmin(tau, sh.sa[c]);
+  }
+  for (int b = wave; b < B; b += waves) {
+    const int mu = sh.mu[b];
+    if (!sh.ok[b] || mu <= 0) {
+      if (first && lane == 0) st.err[b] = 0.0;
+      continue;
+    }
+    const TriLane t = tri(b, mu);
+    double er, ei;
+    tri_expm_e1(t.al, t.be, t.bl, t.on, lane, tau, er, ei);
+    const double n0 = sh.n0[b], g = t.on ? n0 * sh.sg[b * 64 + lane] : 0.0;
+    sh.al[b * 64 + lane] = g * er;
+    sh.be[b * 64 + lane] = g * ei;
+    const double end = __shfl(sqrt(er * er + ei * ei), mu - 1);
+    if (first && lane == 0) st.err[b] = mu == m ? n0 * sh.last[b] * end : 0.0;
+  }
+  __syncthreads();
+}
+
+// psi of one element i of column p: the combination of the element's own
+// entries, which the same thread wrote.
+template <typename V>
+__device__ __forceinline__ void res_combine(const ResShared& sh, const ResArgs& ra, int p, V* psi, const V* U, size_t i) {
+  using T = decltype(V{}.x);
+  const int mu = sh.mu[p];
+  if (!sh.ok[p] || mu <= 0) return;
+  const double* gr = sh.al + p * 64;
+  const double* gi = sh.be + p * 64;
+  const V x0 = psi[i];
+  double ar = gr[0] * (double)x0.x - gi[0] * (double)x0.y;
+  double ai = gr[0] * (double)x0.y + gi[0] * (double)x0.x;
+  for (int j0 = 1; j0 < mu; j0 += 8) {
+    V x[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      x[k] = V{0, 0};
+      if (j0 + k < mu) x[k] = U[(size_t)(j0 + k - 1) * ra.stride + i];
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (j0 + k < mu) {
+        const double cr = gr[j0 + k], ci = gi[j0 + k];
+        ar += cr * (double)x[k].x - ci * (double)x[k].y;
+        ai += cr * (double)x[k].y + ci * (double)x[k].x;
+      }
+  }
+  psi[i] = V{(T)ar, (T)ai};
 }
 
 // u_{j+1} of one row, as the update pass forms it.
@@ -307,12 +438,15 @@ __device__ __forceinline__ void res_alpha(ResShared& sh, const ResArgs& ra, cons
       c = 1.0 / n0;
       d = col.alpha;
       col.sigma = c;
+      sh.n0[b] = n0;
+      sh.sg[b * 64] = c;
       if (first) {
         st.n0[b] = n0;
         st.sigma[b] = c;
       }
       if (!(n0 > 0.0)) {
         active = 0;   // zero vector: nothing to propagate
+        sh.mu[b] = 0;
         if (first) {
           st.mused[b] = 0;
           if (!isfinite(S2)) st.status[b] = QK_ENUMERIC;
@@ -325,11 +459,13 @@ __device__ __forceinline__ void res_alpha(ResShared& sh, const ResArgs& ra, cons
     }
     if (active && !isfinite(col.alpha)) {
       active = 0;
+      sh.ok[b] = 0;
       if (first) {
         st.status[b] = QK_ENUMERIC;
         st.mused[b] = j;
       }
     }
+    sh.al[b * 64 + j] = col.alpha;
     if (active && first) st.alpha[j * B + b] = col.alpha;
     sh.sc[b] = c;
     sh.sd[b] = d;
@@ -346,26 +482,32 @@ __device__ __forceinline__ void res_beta(ResShared& sh, const ResArgs& ra, const
     int active = sh.act[b];
     const double beta = sqrt(norm2);
     if (j + 1 == ra.m) {
+      sh.last[b] = beta;
       if (first) ra.norm2[b] = norm2;
+      if (first && sh.ok[b] && sh.mu[b] == ra.m) st.beta[j * B + b] = beta;
     } else {
       if (active) {
         col.smax = fmax(fmax(col.smax, fabs(col.alpha)), beta);
         if (!isfinite(beta)) {
           active = 0;
+          sh.ok[b] = 0;
           if (first) {
             st.status[b] = QK_ENUMERIC;
             st.mused[b] = j + 1;
           }
         } else if (beta <= ra.rtol * col.smax) {
           active = 0;   // invariant subspace
+          sh.mu[b] = j + 1;
           if (first) st.mused[b] = j + 1;
         }
+        sh.be[b * 64 + j] = beta;
         if (first) st.beta[j * B + b] = beta;
       }
       if (active) {
         sh.sa[b] = 1.0 / beta;
         sh.sb[b] = beta * col.sigma;
         col.sigma = 1.0 / beta;
+        sh.sg[b * 64 + j + 1] = col.sigma;
         if (first) st.sigma[(j + 1) * B + b] = col.sigma;
       }
       sh.act[b] = active;
@@ -375,14 +517,39 @@ __device__ __forceinline__ void res_beta(ResShared& sh, const ResArgs& ra, const
   if (b == 0) sh.go = any && !sh.dead && j + 1 < ra.m;
 }
 
-template <typename T, int KMAX, bool BLOCKED>
-__global__ void __launch_bounds__(kResMaxThreads, 3)
-k_resident(ResArgs ra, typename Cx<T>::V* __restrict__ psi, typename Cx<T>::V* __restrict__ U,
-           typename Cx<T>::V* __restrict__ X, KState st) {
+// Diagonal of state s in column p.
+__device__ __forceinline__ double res_diag(const ResArgs& ra, uint32_t s, const double* f) {
+  double hh = 0.0;
+  for (int i = 0; i < ra.L; ++i) hh += f[i];
+  ModelArgs ma;
+  ma.L = ra.L;
+  ma.pbc = ra.pbc;
+  ma.jz = ra.jz;
+  ma.lmask = (1ull << ra.L) - 1ull;
+  return diag_value<uint32_t>(s, ma, f, 0.5 * hh);
+}
+
+// Whether the form of NT threads goes on to the exponential and the combination.
+// Their code costs the largest complex128 work-groups registers in the loop:
+// the step of the 20-site ring took 337 us with them, 325 us with the kernels
+// that the passes use.
+template <typename T, int NT>
+constexpr bool resident_tail = !(NT > 512 && std::is_same<T, double>::value);
+
+// Loads of LOADS neighbours are in flight at a time, as many as the registers of
+// a thread hold beside everything else: all of them with two waves a SIMD
+// (L = 18: 3.7 us an iteration in three batches, 1.2 at once), seven with three.
+template <typename T, int KMAX, int OLO, int NT, int LOADS>
+__global__ void __launch_bounds__(NT, NT / 256)
+k_resident(ResArgs ra, typename Cx<T>::V* psi, typename Cx<T>::V* U, typename Cx<T>::V* X, KState st) {
   using V = typename Cx<T>::V;
   __shared__ ResShared sh;
+  // offsets of the neighbours: three waves a SIMD leave no registers for them
+  constexpr bool LDSOFF = NT > 512;
+  constexpr bool TAIL = resident_tail<T, NT>;
+  __shared__ uint32_t lo[KMAX * NT];
   const int tid = threadIdx.x, nt = blockDim.x, B = ra.B, Bp = 1 << ra.lbp, p = tid & (Bp - 1);
-  const uint32_t G = gridDim.x;
+  const uint32_t G = ra.groups;
   const uint64_t nel = (uint64_t)ra.D * B;
   // register
   if (tid == 0) {
@@ -393,227 +560,358 @@ k_resident(ResArgs ra, typename Cx<T>::V* __restrict__ psi, typename Cx<T>::V* _
   for (int i = tid; i < kBinomStride * kBinomStride; i += nt) sh.tab[i] = ra.bn[i];
   __syncthreads();
   const uint32_t epoch = sh.epoch, ticket = sh.ticket;
+  const bool late = (ticket & kClosed) != 0 || ticket >= (uint32_t)ra.join_max;
+  uint32_t R = 0;
+  if (!late) {
+    const double* f = ra.fields + (size_t)(p < B ? p : 0) * ra.L;
+    const T g = (T)ra.half_jxy;
+    const ResRows rows{ra, sh.tab, p, (uint32_t)sizeof(V)};
+    // this thread's row
+    const uint32_t row = (ticket * (uint32_t)nt + (uint32_t)tid) >> ra.lbp;
+    const bool has = row < ra.D && p < B;
+    const uint32_t eo = has ? (row * (uint32_t)B + p) * (uint32_t)sizeof(V) : kNoRow;
+    const uint32_t state = has ? ra.states[row] : 0u;
+    rows.template slots<KMAX, OLO>(state, row, lo + tid, NT);
+    const double d = has ? res_diag(ra, state, f) : 0.0;
+    const ResBuf<V> bpsi(psi, nel);
+    V u = bpsi.template ld<0>(eo), um = {0, 0};
+    V un[KMAX];
+#pragma unroll
+    for (int k = 0; k < KMAX; ++k) un[k] = bpsi.template ld<0>(lo[k * NT + tid]);
+    uint32_t off[LDSOFF ? 1 : KMAX];
+#pragma unroll
+    for (int k = 0; k < (LDSOFF ? 0 : KMAX); ++k) off[k] = lo[k * NT + tid];
+    if (tid == 0) {
+      if (ticket == 0) {
+        const long long t0 = wall_clock64();
+        uint32_t n = 0;
+        for (;;) {
+          n = __hip_atomic_load(&ra.ctl->arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (n >= (uint32_t)ra.join_max || wall_clock64() - t0 > kJoinTicks) break;
+          __builtin_amdgcn_s_sleep(1);
+        }
+        n = __hip_atomic_fetch_or(&ra.ctl->arrived, kClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (n > (uint32_t)ra.join_max) n = (uint32_t)ra.join_max;
+        sh.joined = n;
+        word_st(&ra.ctl->joined, ((uint64_t)epoch << 32) | n);
+      } else {
+        uint64_t w;
+        const long long t0 = wall_clock64();
+        do {
+          w = word_ld(&ra.ctl->joined);
+          if (wall_clock64() - t0 > kGiveUpTicks) {
+            sh.dead = 1;
+            break;
+          }
+        } while ((uint32_t)(w >> 32) != epoch || (uint32_t)w == 0u);
+        sh.joined = (uint32_t)w;
+      }
+    }
+    if (tid < B) {
+      sh.sa[tid] = 1.0;
+      sh.sb[tid] = 0.0;
+      sh.act[tid] = 1;
+      sh.mu[tid] = ra.m;
+      sh.ok[tid] = 1;
+    }
+    __syncthreads();
+    R = ticket < sh.joined ? sh.joined : 0u;   // 0: not among the registered
+    const bool first = ticket == 0;
+    if (first && tid < B) {
+      st.mused[tid] = ra.m;
+      st.status[tid] = QK_OK;
+    }
+    ResCol col;
+    const bool wave0 = tid < 64;
+    uint32_t no = epoch;
+    if (R == G) {
+      // every row has its thread: vectors in registers
+      for (int j = 0; j < ra.m; ++j) {
+        const bool mine = p < B && sh.act[p] != 0;
+        const T ca = mine ? (T)sh.sa[p] : (T)0, cb = mine ? (T)sh.sb[p] : (T)0;
+        HopSum<T, KMAX, OLO> sum;
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k) sum.add(k, un[k]);
+        const V w = res_w<T, OLO>(d, g, ca, cb, u, um, sum.total());
+        const ResBuf<V> bx(X + (size_t)(j & 1) * nel, nel);
+        if (mine) bx.template st<kSc1>(eo, w);
+        const bool on = mine && has;
+        const double s1 = on ? (double)u.x * (double)w.x + (double)u.y * (double)w.y : 0.0;
+        if (j == 0) {
+          const double v[2] = {s1, on ? (double)u.x * (double)u.x + (double)u.y * (double)u.y : 0.0};
+          res_partials<2, true>(sh, ra, v);
+        } else {
+          const double v[1] = {s1};
+          res_partials<1, true>(sh, ra, v);
+        }
+        if (wave0) {
+          const int Q = j == 0 ? 2 : 1;
+          res_publish(sh, ra, Q, no, G, ticket);
+          res_alpha(sh, ra, st, j, first, res_collect(sh, ra, Q, no, G), col);
+        }
+        __syncthreads();
+        const bool live = p < B && sh.act[p] != 0;
+        const double c = live ? sh.sc[p] : 0.0, dd = live ? sh.sd[p] : 0.0;
+        const V o = res_next<T>(c, dd, w, u);
+        const double v[1] = {live && has ? (double)o.x * (double)o.x + (double)o.y * (double)o.y : 0.0};
+        res_partials<1, false>(sh, ra, v);
+        if (wave0) res_publish(sh, ra, 1, no + 1, G, ticket);
+        if (j + 1 < ra.m) {
+          if (live) ResBuf<V>(U + (size_t)j * ra.stride, nel).template st<0>(eo, o);
+          // w at the neighbours, while the sums are under way
+#pragma unroll
+          for (int k0 = 0; k0 < KMAX; k0 += LOADS) {
+            V x[LOADS];
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i)
+              if (k0 + i < KMAX) x[i] = bx.template ld<kSc1>(LDSOFF ? lo[(k0 + i) * NT + tid] : off[LDSOFF ? 0 : k0 + i]);
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i)
+              if (k0 + i < KMAX) un[k0 + i] = res_next<T>(c, dd, x[i], un[k0 + i]);
+            __asm__ volatile("" ::: "memory");   // no more loads in flight than that
+          }
+        }
+        um = u;
+        u = o;
+        // |u_m| is needed for the error estimate only
+        if (wave0)
+          res_beta(sh, ra, st, j, first,
+                   j + 1 < ra.m || first || ra.tail == kTailAdaptive ? res_collect(sh, ra, 1, no + 1, G) : 0.0, col);
+        no += 2;
+        __syncthreads();
+        if (!sh.go) break;
+      }
+    } else if (R != 0) {
+      // rows of missing work-groups are dealt out: vectors in memory, agent scope
+      for (int j = 0; j < ra.m; ++j) {
+        const ResBuf<V> bu(j == 0 ? psi : U + (size_t)(j - 1) * ra.stride, nel);
+        const ResBuf<V> bm(j <= 1 ? psi : U + (size_t)(j - 2) * ra.stride, nel);
+        const ResBuf<V> bx(X, nel), bo(U + (size_t)j * ra.stride, nel);
+        const bool mine = p < B && sh.act[p] != 0;
+        const T ca = mine ? (T)sh.sa[p] : (T)0, cb = mine ? (T)sh.sb[p] : (T)0;
+        const int Q = j == 0 ? 2 : 1;
+        for (uint32_t ch = ticket; ch < G; ch += R) {
+          const uint32_t r = (ch * (uint32_t)nt + (uint32_t)tid) >> ra.lbp;
+          const bool on = r < ra.D && mine;
+          const uint32_t e = on ? (r * (uint32_t)B + p) * (uint32_t)sizeof(V) : kNoRow;
+          const uint32_t s = on ? ra.states[r] : 0u;
+          const V x = bu.template ld<kSc1>(e);
+          V xm = {0, 0};
+          if (j > 0) xm = bm.template ld<kSc1>(e);
+          HopSum<T, KMAX, OLO> sum;
+          rows.template slots<KMAX, OLO>(s, r, lo + tid, NT);
+#pragma unroll 1
+          for (int k = 0; k < KMAX; ++k) sum.add(k, bu.template ld<kSc1>(lo[k * NT + tid]));
+          const V w = res_w<T, OLO>(on ? res_diag(ra, s, f) : 0.0, g, ca, cb, x, xm, sum.total());
+          bx.template st<kSc1>(e, w);
+          const double v[2] = {on ? (double)x.x * (double)w.x + (double)x.y * (double)w.y : 0.0,
+                               on ? (double)x.x * (double)x.x + (double)x.y * (double)x.y : 0.0};
+          res_partials<2, true>(sh, ra, v);
+          if (wave0) res_publish(sh, ra, Q, no, G, ch);
+          __syncthreads();
+        }
+        if (wave0) res_alpha(sh, ra, st, j, first, res_collect(sh, ra, Q, no, G), col);
+        __syncthreads();
+        const bool live = p < B && sh.act[p] != 0;
+        const double c = live ? sh.sc[p] : 0.0, dd = live ? sh.sd[p] : 0.0;
+        for (uint32_t ch = ticket; ch < G; ch += R) {
+          const uint32_t r = (ch * (uint32_t)nt + (uint32_t)tid) >> ra.lbp;
+          const bool on = r < ra.D && live;
+          const uint32_t e = on ? (r * (uint32_t)B + p) * (uint32_t)sizeof(V) : kNoRow;
+          const V o = res_next<T>(c, dd, bx.template ld<kSc1>(e), bu.template ld<kSc1>(e));
+          if (j + 1 < ra.m) bo.template st<kSc1>(e, o);
+          const double v[1] = {on ? (double)o.x * (double)o.x + (double)o.y * (double)o.y : 0.0};
+          res_partials<1, true>(sh, ra, v);
+          if (wave0) res_publish(sh, ra, 1, no + 1, G, ch);
+          __syncthreads();
+        }
+        if (wave0)
+          res_beta(sh, ra, st, j, first,
+                   j + 1 < ra.m || first || ra.tail == kTailAdaptive ? res_collect(sh, ra, 1, no + 1, G) : 0.0, col);
+        no += 2;
+        __syncthreads();
+        if (!sh.go) break;
+      }
+    }
+    if (TAIL && R != 0 && ra.tail != kTailNone && !sh.dead) {
+      res_coefs(sh, ra, st, first);
+      for (uint32_t ch = ticket; ch < G; ch += R) {   // its own row only where R == G
+        const uint32_t r = (ch * (uint32_t)nt + (uint32_t)tid) >> ra.lbp;
+        if (r < ra.D && p < B) res_combine(sh, ra, p, psi, U, (size_t)r * B + p);
+      }
+    }
+    __syncthreads();
+    if (tid == 0 && sh.dead)
+      for (int b = 0; b < B; ++b) st.status[b] = QK_ENUMERIC;
+  }
+  // the last work-group, late ones included, makes room for the next launch
+  if (tid == 0 &&
+      __hip_atomic_fetch_add(&ra.ctl->left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == G - 1) {
+    __hip_atomic_store(&ra.ctl->arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&ra.ctl->left, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    word_st(&ra.ctl->joined, 0ull);
+    __hip_atomic_store(&ra.ctl->epoch, epoch - 1u + 2u * (uint32_t)ra.m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// Rows that fit one work-group: nothing leaves it but the basis.  The current
+// vector lies in LDS; sums go through LDS once, and every thread computes its
+// column's scalars for itself, so an iteration has two barriers.
+constexpr int kOneThreads = 1024;
+template <typename T, int KMAX, int OLO>
+__global__ void __launch_bounds__(kOneThreads)
+k_resident_one(ResArgs ra, typename Cx<T>::V* psi, typename Cx<T>::V* U, KState st) {
+  using V = typename Cx<T>::V;
+  __shared__ ResShared sh;
+  __shared__ uint32_t lo[KMAX * kOneThreads];
+  __shared__ V ul[kOneThreads + 1];                        // u_j of the rows, and a zero
+  __shared__ double red[2][2 * kOneThreads / 64 * kResMaxLanes];   // of the two sums in turn
+  const int tid = threadIdx.x, nt = blockDim.x, B = ra.B, Bp = 1 << ra.lbp, p = tid & (Bp - 1);
+  const int lane = tid & 63, wave = tid >> 6, waves = nt >> 6;
+  for (int i = tid; i < kBinomStride * kBinomStride; i += nt) sh.tab[i] = ra.bn[i];
+  const uint32_t row = (uint32_t)tid >> ra.lbp;
+  const bool has = row < ra.D && p < B;
+  const size_t e = (size_t)row * B + p;
+  const uint32_t state = has ? ra.states[row] : 0u;
+  V u = has ? psi[e] : V{0, 0}, um = {0, 0};
+  ul[tid] = u;
+  if (tid == 0) {
+    ul[nt] = V{0, 0};
+    sh.dead = 0;
+  }
+  __syncthreads();
   const double* f = ra.fields + (size_t)(p < B ? p : 0) * ra.L;
   const T g = (T)ra.half_jxy;
-  double hh = 0.0;
-  for (int i = 0; i < ra.L; ++i) hh += f[i];
-  ModelArgs ma;
-  ma.L = ra.L;
-  ma.pbc = ra.pbc;
-  ma.jz = ra.jz;
-  ma.lmask = (1ull << ra.L) - 1ull;
-  // offset of the partner of state s (row r) across bond k, kNoRow if the
-  // bond's bits agree; pc: set bits below k
-  auto partner = [&](uint32_t s, uint32_t r, int k, int pc) -> uint32_t {
-    uint32_t q;
-    if (k < ra.L - 1) {
-      const uint32_t b0 = (s >> k) & 1u;
-      const uint32_t c = sh.tab[k * kBinomStride + pc];
-      if (b0 == ((s >> (k + 1)) & 1u)) return kNoRow;
-      q = b0 ? r + c : r - c;
-    } else {
-      if (((s ^ (s >> (ra.L - 1))) & 1u) == 0u) return kNoRow;
-      q = cns_rank<uint32_t>(s ^ (1u | (1u << (ra.L - 1))), sh.tab);
-    }
-    return (q * (uint32_t)B + p) * (uint32_t)sizeof(V);
-  };
-  // this thread's row
-  const uint32_t row = (blockIdx.x * (uint32_t)nt + (uint32_t)tid) >> ra.lbp;
-  const bool has = row < ra.D && p < B;
-  const uint32_t eo = has ? (row * (uint32_t)B + p) * (uint32_t)sizeof(V) : kNoRow;
-  const uint32_t state = has ? ra.states[row] : 0u;
-  uint32_t off[KMAX];
+  uint32_t off[KMAX];   // places in ul
   {
-    int pc = 0;
+    ResArgs one = ra;
+    one.B = Bp;   // columns of ul
+    ResRows{one, sh.tab, p, 1u}.template slots<KMAX, OLO>(state, row, lo + tid, kOneThreads);
 #pragma unroll
     for (int k = 0; k < KMAX; ++k) {
-      off[k] = kNoRow;
-      if (k < ra.nbonds) off[k] = partner(state, row, k, pc);
-      pc += (int)((state >> k) & 1u);
+      off[k] = lo[k * kOneThreads + tid];
+      if (off[k] == kNoRow) off[k] = (uint32_t)nt;
     }
   }
-  // where the groups of four hops of a state end (HopSum)
-  auto flushes = [&](uint32_t s) -> uint32_t {
-    uint32_t m = 0;
-    int n = 0;
-    if (BLOCKED)
-      for (int k = ra.olo; k < ra.L - 1; ++k)
-        if (((s >> k) ^ (s >> (k + 1))) & 1u)
-          if ((++n & 3) == 0) m |= 1u << k;
-    return m;
+  const double d = has ? res_diag(ra, state, f) : 0.0;
+  // the sum over the work-group of one quantity of a column, its per-wave sums
+  // in r[wave * Bp + column]
+  auto total = [&](const double* r) -> double {
+    if (Bp == 1) {
+      double v = lane < waves ? r[lane] : 0.0;   // at most 16
+      v = dpp_add<0x111, 0xf>(v);
+      v = dpp_add<0x112, 0xf>(v);
+      v = dpp_add<0x114, 0xf>(v);
+      v = dpp_add<0x118, 0xf>(v);
+      const uint64_t b = __builtin_bit_cast(uint64_t, v);
+      const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, 15);
+      const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 15);
+      return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+    }
+    double t = 0.0;
+    for (int w = 0; w < waves; ++w) t += r[w * Bp + p];
+    return t;
   };
-  uint32_t flush = flushes(state);
-  const double d = has ? diag_value<uint32_t>(state, ma, f, 0.5 * hh) : 0.0;
-  const ResBuf<V> bpsi(psi, nel);
-  V u = bpsi.template ld<0>(eo), um = {0, 0};
-  V un[KMAX];
+  const bool rec = tid < B;   // records its column's results
+  bool act = p < B, ok = true;
+  int mu = ra.m;
+  double sa = 1.0, sb = 0.0, sigma = 0.0, smax = 0.0, n0 = 0.0, last = 0.0;
+  for (int j = 0; j < ra.m; ++j) {
+    const T ca = act ? (T)sa : (T)0, cb = act ? (T)sb : (T)0;
+    HopSum<T, KMAX, OLO> sum;
 #pragma unroll
-  for (int k = 0; k < KMAX; ++k) un[k] = bpsi.template ld<0>(off[k]);
-  if (tid == 0) {
-    if ((ticket & kClosed) || ticket >= (uint32_t)ra.join_max) {
-      sh.joined = 0;   // too late
-    } else if (ticket == 0) {
-      const long long t0 = wall_clock64();
-      uint32_t n = 0;
-      for (;;) {
-        n = __hip_atomic_load(&ra.ctl->arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (n >= (uint32_t)ra.join_max || wall_clock64() - t0 > kJoinTicks) break;
-        __builtin_amdgcn_s_sleep(1);
+    for (int k = 0; k < KMAX; ++k) sum.add(k, ul[off[k]]);
+    const V w = res_w<T, OLO>(d, g, ca, cb, u, um, sum.total());
+    const bool on = act && has;
+    const double t1 = res_wave_sum(on ? (double)u.x * (double)w.x + (double)u.y * (double)w.y : 0.0, Bp);
+    if (lane < Bp) red[0][wave * Bp + lane] = t1;
+    if (j == 0) {
+      const double t2 = res_wave_sum(on ? (double)u.x * (double)u.x + (double)u.y * (double)u.y : 0.0, Bp);
+      if (lane < Bp) red[0][(waves + wave) * Bp + lane] = t2;
+    }
+    __syncthreads();
+    const double S = total(red[0]);
+    double c = 1.0, dd, alpha;
+    if (j == 0) {
+      const double S2 = total(red[0] + waves * Bp);
+      n0 = sqrt(S2);
+      alpha = S / S2;
+      c = 1.0 / n0;
+      dd = alpha;
+      sigma = c;
+      if (act && !(n0 > 0.0)) {
+        act = false;   // zero vector: nothing to propagate
+        mu = 0;
+        if (!isfinite(S2)) ok = false;
       }
-      n = __hip_atomic_fetch_or(&ra.ctl->arrived, kClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (n > (uint32_t)ra.join_max) n = (uint32_t)ra.join_max;
-      sh.joined = n;
-      word_st(&ra.ctl->joined, ((uint64_t)epoch << 32) | n);
     } else {
-      uint64_t w;
-      const long long t0 = wall_clock64();
-      do {
-        w = word_ld(&ra.ctl->joined);
-        if (wall_clock64() - t0 > kGiveUpTicks) {
-          sh.dead = 1;
-          break;
-        }
-      } while ((uint32_t)(w >> 32) != epoch || (uint32_t)w == 0u);
-      sh.joined = (uint32_t)w;
+      alpha = sigma * S;
+      dd = alpha * sigma;
     }
-  }
-  if (tid < B) {
-    sh.sa[tid] = 1.0;
-    sh.sb[tid] = 0.0;
-    sh.act[tid] = 1;
-  }
-  __syncthreads();
-  const uint32_t R = sh.joined;
-  const bool member = R != 0 && (ticket & ~kClosed) < R;
-  const bool first = member && ticket == 0;
-  if (first && tid < B) {
-    st.mused[tid] = ra.m;
-    st.status[tid] = QK_OK;
-  }
-  ResCol col;
-  const bool wave0 = tid < 64;
-  uint32_t no = epoch;
-  if (member && R == G) {
-    // every row has its thread: vectors in registers
-    for (int j = 0; j < ra.m; ++j) {
-      const bool mine = p < B && sh.act[p] != 0;
-      const T ca = mine ? (T)sh.sa[p] : (T)0, cb = mine ? (T)sh.sb[p] : (T)0;
-      HopSum<T, BLOCKED> sum;
-      if (BLOCKED) __asm__ volatile("" : "+v"(flush));   // its bits as lane masks would not fit the scalar registers
-#pragma unroll
-      for (int k = 0; k < KMAX; ++k)
-        if (!BLOCKED || k < ra.nbonds) sum.add(ra, k, un[k], flush);
-      const V w = res_w<T, BLOCKED>(d, g, ca, cb, u, um, sum.total());
-      const ResBuf<V> bx(X + (size_t)(j & 1) * nel, nel);
-      if (mine) bx.template st<kSc1>(eo, w);
-      const bool on = mine && has;
-      const double s1 = on ? (double)u.x * (double)w.x + (double)u.y * (double)w.y : 0.0;
-      if (j == 0) {
-        const double v[2] = {s1, on ? (double)u.x * (double)u.x + (double)u.y * (double)u.y : 0.0};
-        res_partials<2, true>(sh, ra, v);
+    if (act && !isfinite(alpha)) {
+      act = false;
+      ok = false;
+      mu = j;
+    }
+    const double sj = sigma;
+    const V o = act ? res_next<T>(c, dd, w, u) : V{0, 0};
+    ul[tid] = o;
+    if (act && has && j + 1 < ra.m) U[(size_t)j * ra.stride + e] = o;
+    const double t3 = res_wave_sum(act && has ? (double)o.x * (double)o.x + (double)o.y * (double)o.y : 0.0, Bp);
+    if (lane < Bp) red[1][wave * Bp + lane] = t3;
+    if (rec && act) {
+      sh.al[tid * 64 + j] = alpha;
+      sh.sg[tid * 64 + j] = sj;
+    }
+    __syncthreads();
+    um = u;
+    u = o;
+    const double beta = sqrt(total(red[1]));
+    if (j + 1 == ra.m) {
+      last = beta;
+    } else if (act) {
+      smax = fmax(fmax(smax, fabs(alpha)), beta);
+      if (rec) sh.be[tid * 64 + j] = beta;
+      if (!isfinite(beta)) {
+        act = false;
+        ok = false;
+        mu = j + 1;
+      } else if (beta <= ra.rtol * smax) {
+        act = false;   // invariant subspace
+        mu = j + 1;
       } else {
-        const double v[1] = {s1};
-        res_partials<1, true>(sh, ra, v);
+        sb = beta * sigma;
+        sa = 1.0 / beta;
+        sigma = sa;
       }
-      if (wave0) {
-        const int Q = j == 0 ? 2 : 1;
-        res_publish(sh, ra, Q, no, G, blockIdx.x);
-        res_alpha(sh, ra, st, j, first, res_collect(sh, ra, Q, no, G), col);
-      }
-      __syncthreads();
-      const bool live = p < B && sh.act[p] != 0;
-      const double c = live ? sh.sc[p] : 0.0, dd = live ? sh.sd[p] : 0.0;
-      const V o = res_next<T>(c, dd, w, u);
-      const double v[1] = {live && has ? (double)o.x * (double)o.x + (double)o.y * (double)o.y : 0.0};
-      res_partials<1, false>(sh, ra, v);
-      if (wave0) res_publish(sh, ra, 1, no + 1, G, blockIdx.x);
-      if (j + 1 < ra.m) {
-        if (live) ResBuf<V>(U + (size_t)j * ra.stride, nel).template st<0>(eo, o);
-        // w at the neighbours, while the sums are under way
-#pragma unroll
-        for (int k0 = 0; k0 < KMAX; k0 += kResLoads) {
-          V x[kResLoads];
-#pragma unroll
-          for (int i = 0; i < kResLoads; ++i)
-            if (k0 + i < KMAX) x[i] = bx.template ld<kSc1>(off[k0 + i]);
-#pragma unroll
-          for (int i = 0; i < kResLoads; ++i)
-            if (k0 + i < KMAX) un[k0 + i] = res_next<T>(c, dd, x[i], un[k0 + i]);
-          __asm__ volatile("" ::: "memory");   // no more loads in flight than registers hold
-        }
-      }
-      um = u;
-      u = o;
-      if (wave0) res_beta(sh, ra, st, j, first, res_collect(sh, ra, 1, no + 1, G), col);
-      no += 2;
-      __syncthreads();
-      if (!sh.go) break;
     }
-  } else if (member) {
-    // rows of missing work-groups are dealt out: vectors in memory
-    for (int j = 0; j < ra.m; ++j) {
-      const ResBuf<V> bu(j == 0 ? psi : U + (size_t)(j - 1) * ra.stride, nel);
-      const ResBuf<V> bm(j <= 1 ? psi : U + (size_t)(j - 2) * ra.stride, nel);
-      const ResBuf<V> bx(X, nel), bo(U + (size_t)j * ra.stride, nel);
-      const bool mine = p < B && sh.act[p] != 0;
-      const T ca = mine ? (T)sh.sa[p] : (T)0, cb = mine ? (T)sh.sb[p] : (T)0;
-      const int Q = j == 0 ? 2 : 1;
-      for (uint32_t ch = ticket; ch < G; ch += R) {
-        const uint32_t r = (ch * (uint32_t)nt + (uint32_t)tid) >> ra.lbp;
-        const bool on = r < ra.D && mine;
-        const uint32_t e = on ? (r * (uint32_t)B + p) * (uint32_t)sizeof(V) : kNoRow;
-        const uint32_t s = on ? ra.states[r] : 0u;
-        const V x = bu.template ld<kSc1>(e);
-        V xm = {0, 0};
-        if (j > 0) xm = bm.template ld<kSc1>(e);
-        HopSum<T, BLOCKED> sum;
-        const uint32_t fl = flushes(s);
-        int pc = 0;
-        for (int k = 0; k < ra.nbonds; ++k) {
-          sum.add(ra, k, bu.template ld<kSc1>(partner(s, r, k, pc)), fl);
-          pc += (int)((s >> k) & 1u);
-        }
-        const V w = res_w<T, BLOCKED>(on ? diag_value<uint32_t>(s, ma, f, 0.5 * hh) : 0.0, g, ca, cb, x, xm, sum.total());
-        bx.template st<kSc1>(e, w);
-        const double v[2] = {on ? (double)x.x * (double)w.x + (double)x.y * (double)w.y : 0.0,
-                             on ? (double)x.x * (double)x.x + (double)x.y * (double)x.y : 0.0};
-        res_partials<2, true>(sh, ra, v);
-        if (wave0) res_publish(sh, ra, Q, no, G, ch);
-        __syncthreads();
-      }
-      if (wave0) res_alpha(sh, ra, st, j, first, res_collect(sh, ra, Q, no, G), col);
-      __syncthreads();
-      const bool live = p < B && sh.act[p] != 0;
-      const double c = live ? sh.sc[p] : 0.0, dd = live ? sh.sd[p] : 0.0;
-      for (uint32_t ch = ticket; ch < G; ch += R) {
-        const uint32_t r = (ch * (uint32_t)nt + (uint32_t)tid) >> ra.lbp;
-        const bool on = r < ra.D && live;
-        const uint32_t e = on ? (r * (uint32_t)B + p) * (uint32_t)sizeof(V) : kNoRow;
-        const V o = res_next<T>(c, dd, bx.template ld<kSc1>(e), bu.template ld<kSc1>(e));
-        if (j + 1 < ra.m) bo.template st<kSc1>(e, o);
-        const double v[1] = {on ? (double)o.x * (double)o.x + (double)o.y * (double)o.y : 0.0};
-        res_partials<1, true>(sh, ra, v);
-        if (wave0) res_publish(sh, ra, 1, no + 1, G, ch);
-        __syncthreads();
-      }
-      if (wave0) res_beta(sh, ra, st, j, first, res_collect(sh, ra, 1, no + 1, G), col);
-      no += 2;
-      __syncthreads();
-      if (!sh.go) break;
-    }
+    // every wave holds every column: the same answer in all of them
+    if (!__any(act)) break;
+  }
+  if (rec) {
+    const int b = tid;
+    sh.mu[b] = mu;
+    sh.ok[b] = ok ? 1 : 0;
+    sh.n0[b] = n0;
+    sh.last[b] = last;
+    st.mused[b] = mu;
+    st.status[b] = ok ? QK_OK : QK_ENUMERIC;
+    st.n0[b] = n0;
+    if (ok && mu == ra.m) sh.be[b * 64 + ra.m - 1] = last;
   }
   __syncthreads();
-  if (tid == 0) {
-    if (sh.dead)
-      for (int b = 0; b < B; ++b) st.status[b] = QK_ENUMERIC;
-    // the last work-group, late ones included, makes room for the next launch
-    if (__hip_atomic_fetch_add(&ra.ctl->left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == G - 1) {
-      __hip_atomic_store(&ra.ctl->arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(&ra.ctl->left, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      word_st(&ra.ctl->joined, 0ull);
-      __hip_atomic_store(&ra.ctl->epoch, epoch - 1u + 2u * (uint32_t)ra.m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int i = tid; i < B * 64; i += nt) {
+    const int b = i >> 6, j = i & 63, n = sh.mu[b];
+    if (j < n) {
+      st.alpha[j * B + b] = sh.al[i];
+      st.sigma[j * B + b] = sh.sg[i];
+      if (j + 1 < n || (sh.ok[b] && n == ra.m)) st.beta[j * B + b] = sh.be[i];
     }
   }
+  if (ra.tail == kTailNone) return;
+  __syncthreads();
+  res_coefs(sh, ra, st, true);
+  if (has) res_combine(sh, ra, p, psi, U, e);
 }
 
 // ------------------------------------------------------------------- host
@@ -628,49 +926,93 @@ static uint64_t resident_lanes(const qk_krylov* k) {
   return Bp <= (uint64_t)kResMaxLanes && lanes <= (uint64_t)kResMaxThreads * kResMaxGroups ? lanes : 0;
 }
 
-// Threads per work-group and work-groups: 256 threads up to 256 work-groups,
-// then larger work-groups.
-static void resident_grid(uint64_t lanes, int* threads, int* groups) {
-  int nt = 256;
-  if (lanes > (uint64_t)nt * kResMaxGroups) nt = (int)((lanes + kResMaxGroups * 64 - 1) / (kResMaxGroups * 64)) * 64;
-  *threads = nt;
-  *groups = (int)((lanes + nt - 1) / nt);
-}
+// Threads per work-group and work-groups for a number of lanes; one work-group
+// is the form of its own.  Otherwise 256 threads up to 256 work-groups, then
+// larger work-groups.
+struct ResShape {
+  int threads, groups;
+};
 
-static size_t resident_words(int groups, int lanes_per_row) { return (size_t)2 * groups * 2 * lanes_per_row * 2; }
+static ResShape resident_shape(uint64_t lanes, uint64_t per_row) {
+  if (lanes <= (uint64_t)kOneThreads) return {(int)((lanes + 63) / 64) * 64, 1};
+  int nt = 256;
+  while (nt < 512 && (lanes + nt - 1) / nt * per_row > 256) nt += 64;   // one round of the wave that collects
+  if (lanes > (uint64_t)nt * kResMaxGroups) nt = (int)((lanes + kResMaxGroups * 64 - 1) / (kResMaxGroups * 64)) * 64;
+  return {nt, (int)((lanes + nt - 1) / nt)};
+}
 
 void resident_bytes(const qk_krylov* k, size_t* head, size_t* body) {
   *head = *body = 0;
   const uint64_t lanes = resident_lanes(k);
   if (!lanes) return;
-  int nt, G;
-  resident_grid(lanes, &nt, &G);
-  *head = sizeof(ResCtl) + sizeof(uint64_t) * resident_words(G, (int)(lanes / (uint64_t)k->D));
-  *body = 2 * (size_t)k->D * k->batch * (k->dtype == QK_C128 ? 16 : 8);
+  const size_t per_row = (size_t)(lanes / (uint64_t)k->D);
+  const ResShape sp = resident_shape(lanes, per_row);
+  *head = sizeof(ResCtl);
+  if (sp.groups == 1) return;
+  *head += sizeof(uint64_t) * (size_t)2 * sp.groups * 2 * per_row * 2;
+  *body = (size_t)2 * k->D * k->batch * (k->dtype == QK_C128 ? 16 : 8);
 }
 
-template <typename T, int KMAX, bool BLOCKED>
-static void resident_launch(const ResArgs& ra, int G, int nt, void* psi, void* U, void* X, const KState& st,
-                            hipStream_t s) {
-  using V = typename Cx<T>::V;
-  hipLaunchKernelGGL((k_resident<T, KMAX, BLOCKED>), dim3(G), dim3(nt), 0, s, ra, (V*)psi, (V*)U, (V*)X, st);
+struct ResLaunch {
+  ResArgs ra;
+  ResShape sp;
+  void *psi, *U, *X;
+  KState st;
+  hipStream_t s;
+  template <typename T, int KMAX, int OLO>
+  void one() const {
+    using V = typename Cx<T>::V;
+    hipLaunchKernelGGL((k_resident_one<T, KMAX, OLO>), dim3(1), dim3(sp.threads), 0, s, ra, (V*)psi, (V*)U, st);
+  }
+  template <typename T, int KMAX, int OLO, int NT, int LOADS>
+  void many() const {
+    using V = typename Cx<T>::V;
+    hipLaunchKernelGGL((k_resident<T, KMAX, OLO, NT, LOADS>), dim3(sp.groups), dim3(sp.threads), 0, s, ra,
+                       (V*)psi, (V*)U, (V*)X, st);
+  }
+  // the bonds that a thread keeps registers for: 14, 17 or 20
+  template <typename T, int OLO>
+  void go() const {
+    constexpr int LOADS = std::is_same<T, double>::value ? 7 : 20;   // of the largest work-groups
+    if (sp.groups == 1) {
+      if (OLO == 0 && ra.nbonds <= 14) one<T, 14, 0>();
+      else one<T, 20, OLO>();
+    } else if (sp.threads <= 512) {
+      if (OLO == 0 && ra.nbonds <= 14) many<T, 14, 0, 512, 14>();
+      else if (OLO == 0 && ra.nbonds <= 17) many<T, 17, 0, 512, 17>();
+      else many<T, 20, OLO, 512, 20>();
+    } else {
+      many<T, 20, OLO, kResMaxThreads, LOADS>();
+    }
+  }
+};
+
+// Low bits of the decomposition whose order complex64 follows, 0: none.
+static int resident_olo(const qk_krylov* k) { return k->dtype == QK_C128 || k->H->llo <= 0 ? 0 : k->H->llo; }
+
+// Whether the next step takes it: a decomposition that the caller has chosen
+// (qk_launch_shape) may ask for an order of summation that it has no form for.
+bool resident_covers(const qk_krylov* k) {
+  const int olo = resident_olo(k);
+  return k->d_res && (olo == 0 || olo == 9 || olo == 10);
 }
 
-qk_status launch_resident(qk_krylov* k, void* psi, double rtol, hipStream_t s) {
+qk_status launch_resident(qk_krylov* k, void* psi, double rtol, double tau, StepUpTo upto, const AdaptiveStep* ad,
+                          hipStream_t s, bool* done) {
   const qk_ham* H = k->H;
+  ResLaunch rl{};
   const uint64_t lanes = resident_lanes(k);
-  int nt, G;
-  resident_grid(lanes, &nt, &G);
-  ResArgs ra{};
+  rl.sp = resident_shape(lanes, lanes / (uint64_t)k->D);
+  ResArgs& ra = rl.ra;
   ra.L = H->basis->L;
   ra.pbc = H->p.pbc;
   ra.B = k->batch;
   while ((1 << ra.lbp) < k->batch) ++ra.lbp;
   ra.m = k->m;
-  ra.olo = H->llo > 0 ? H->llo : ra.L + 1;
   ra.nbonds = ra.pbc ? ra.L : ra.L - 1;
   ra.D = (uint32_t)k->D;
-  ra.join_max = k->res_join > 0 ? std::min(G, k->res_join) : G;
+  ra.groups = rl.sp.groups;
+  ra.join_max = k->res_join > 0 ? std::min(ra.groups, k->res_join) : ra.groups;
   ra.half_jxy = 0.5 * H->p.jxy;
   ra.jz = H->p.jz;
   ra.rtol = rtol;
@@ -680,21 +1022,22 @@ qk_status launch_resident(qk_krylov* k, void* psi, double rtol, hipStream_t s) {
   ra.stride = k->ustride;
   ra.ctl = (ResCtl*)k->d_res;
   ra.words = (uint64_t*)((char*)k->d_res + sizeof(ResCtl));
+  const bool whole = k->dtype != QK_C128 || rl.sp.threads <= 512 || rl.sp.groups == 1;   // resident_tail
+  ra.tail = !whole || upto == StepUpTo::basis ? kTailNone : ad ? kTailAdaptive : kTailStep;
   ra.norm2 = k->d_partB;
-  void* X = k->d_X;
-  const KState st = make_kstate(k);
-  // the bonds that a thread keeps registers for: 14, 17 or 20
-  if (k->dtype == QK_C128) {
-    if (ra.nbonds <= 14) resident_launch<double, 14, false>(ra, G, nt, psi, k->d_U, X, st, s);
-    else if (ra.nbonds <= 17) resident_launch<double, 17, false>(ra, G, nt, psi, k->d_U, X, st, s);
-    else resident_launch<double, 20, false>(ra, G, nt, psi, k->d_U, X, st, s);
-  } else if (ra.olo > ra.L) {
-    if (ra.nbonds <= 14) resident_launch<float, 14, false>(ra, G, nt, psi, k->d_U, X, st, s);
-    else if (ra.nbonds <= 17) resident_launch<float, 17, false>(ra, G, nt, psi, k->d_U, X, st, s);
-    else resident_launch<float, 20, false>(ra, G, nt, psi, k->d_U, X, st, s);
-  } else {
-    resident_launch<float, 20, true>(ra, G, nt, psi, k->d_U, X, st, s);
-  }
+  *done = whole || upto == StepUpTo::basis;
+  ra.tau = tau;
+  ra.tol = ad ? ad->tol : 0.0;
+  rl.psi = psi;
+  rl.U = k->d_U;
+  rl.X = k->d_X;
+  rl.st = make_kstate(k);
+  rl.s = s;
+  const int olo = resident_olo(k);
+  if (k->dtype == QK_C128) rl.go<double, 0>();
+  else if (olo == 0) rl.go<float, 0>();
+  else if (olo == 9) rl.go<float, 9>();
+  else rl.go<float, 10>();
   QK_HIP(hipGetLastError());
   return QK_OK;
 }

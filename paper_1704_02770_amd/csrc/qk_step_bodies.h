@@ -262,6 +262,34 @@ __device__ __forceinline__ TriLane tri_lane(const KState& st, int B, int b, int 
   return t;
 }
 
+// Step-size control of one adaptive step (the rule of Expokit, which the
+// paper's runs use through SLEPc): starting from tau_max, the step tau of
+// a column is accepted when the estimate err(tau) = ||psi|| beta_m
+// |[exp(-i tau T)]_{m,1}| is at most 1.2 tau tol, and otherwise replaced by
+// 0.9 tau (tau tol / err)^(1 / (m - 1)), kept within [tau / 10, 0.9 tau].  The
+// Krylov basis does not depend on tau, so only the small exponential is
+// recomputed.  By one wave (lane i); scale = ||psi|| beta_m; returns the
+// accepted step, next = suggested next step (0.9 tau (tau tol / err)^(1/(m-1)),
+// at most 10 tau).
+__device__ __forceinline__ double step_size(const TriLane& t, int m, int i, double scale, double tau_max, double tol,
+                                            double& next) {
+  const double xm = 1.0 / (double)(m - 1);
+  double err = 0.0, tau = tau_max;
+  for (int it = 0; it < 60; ++it) {
+    double er, ei;
+    tri_expm_e1(t.al, t.be, t.bl, t.on, i, tau, er, ei);
+    err = scale * __shfl(sqrt(er * er + ei * ei), m - 1);
+    if (err <= 1.2 * tau * tol) break;
+    double nt = 0.9 * tau * pow(tau * tol / err, xm);
+    if (!(nt >= 0.1 * tau)) nt = 0.1 * tau;   // also catches a NaN estimate
+    if (nt > 0.9 * tau) nt = 0.9 * tau;
+    tau = nt;
+  }
+  next = (err > 0.0) ? 0.9 * tau * pow(tau * tol / err, xm) : 10.0 * tau;
+  if (!(next <= 10.0 * tau)) next = 10.0 * tau;
+  return tau;
+}
+
 // c = exp(-i tau T) e_1 for the tridiagonal T of the Lanczos recurrence
 // (tri_expm_e1), times ||psi|| and the stored-vector scales, plus the
 // a-posteriori error estimate ||psi|| beta_m |c_m|.  With tau_dev != NULL the

@@ -28,6 +28,7 @@
 // forward step from psi_{K-1-k}: W = conj(V'), T' = T_{K-1-k}, and
 // conj(W_rc) = V'_rc.  The backward sweep reads the forward bases of the
 // steps k and K-1-k instead of propagating the costate.
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <new>
@@ -38,6 +39,7 @@
 
 namespace qk {
 
+constexpr int kGradSteps = 16;     // steps of one launch of the contraction, where their bases are kept
 constexpr int kGradMaxM = 32;      // Krylov dimension of the gradient (register-held basis rows)
 constexpr int kGaussNodes = 24;
 
@@ -72,13 +74,38 @@ static GaussRule gauss_legendre() {
   return g;
 }
 
-// C = integral_0^dt conj(q(tau)) p(tau)^T dtau by the Gauss rule: block n
-// (one wavefront; lane i owns component i of p and q) evaluates node n and
-// writes its weighted term w_n conj(q_c) p_d to Cn[n][c][d] (complex).
+// The steps that one launch takes, y = 0, 1, ... in the order of the backward
+// sweep: the arrays of step y of the forward recurrence lie y entries below
+// those of fw in a bank, those of the mirrored one y entries above bw.
+struct GradSteps {
+  KState fw, bw;
+  size_t coef;             // doubles of one entry of the coefficients' bank (ints: 2)
+  const double2* psi;      // psi_t of y = 0; of the others D elements below each other
+  const double2* vm;       // psi of the mirrored step; D above
+  const double2 *Uf, *Ub;  // their bases; basis elements below and above
+  size_t D, basis;
+  __device__ KState fwd(int y) const { return at(fw, -(ptrdiff_t)(y * coef), -2 * (ptrdiff_t)y); }
+  __device__ KState bwd(int y) const { return at(bw, (ptrdiff_t)(y * coef), 2 * (ptrdiff_t)y); }
+  __device__ static KState at(KState k, ptrdiff_t d, ptrdiff_t i) {
+    k.alpha += d;
+    k.beta += d;
+    k.sigma += d;
+    k.n0 += d;
+    k.mused += i;
+    k.status += i;
+    return k;
+  }
+};
+
+// C = integral_0^dt conj(q(tau)) p(tau)^T dtau by the Gauss rule: block (n, y)
+// (one wavefront; lane i owns component i of p and q) evaluates node n of step
+// y and writes its weighted term w_n conj(q_c) p_d to Cn[y][n][c][d] (complex).
 __global__ void __launch_bounds__(64)
-k_grad_nodes(KState fw, KState bw, double dt, GaussRule gr, double* __restrict__ Cn) {
+k_grad_nodes(GradSteps gs, double dt, GaussRule gr, double* __restrict__ Cn) {
   __shared__ double Pr[64], Pi[64];
   const int i = threadIdx.x, n = blockIdx.x;
+  const KState fw = gs.fwd(blockIdx.y), bw = gs.bwd(blockIdx.y);
+  Cn += (size_t)blockIdx.y * 2 * kGradMaxM * kGradMaxM * kGaussNodes;
   const int muf = fw.mused[0], mub = bw.mused[0];
   if (fw.status[0] != QK_OK || bw.status[0] != QK_OK || muf <= 0 || mub <= 0) return;   // k_grad_coeffs writes zeros
   const bool onf = i < muf, onb = i < mub;
@@ -106,9 +133,12 @@ k_grad_nodes(KState fw, KState bw, double dt, GaussRule gr, double* __restrict__
 }
 
 // C~_cd = sigma'_c sigma_d C_cd for the stored (unnormalised) basis vectors:
-// the node terms summed in node order (one thread per entry).
+// the node terms summed in node order (one thread per entry, a block a step).
 __global__ void __launch_bounds__(kGradMaxM * kGradMaxM)
-k_grad_coeffs(KState fw, KState bw, const double* __restrict__ Cn, double* __restrict__ Ct) {
+k_grad_coeffs(GradSteps gs, const double* __restrict__ Cn, double* __restrict__ Ct) {
+  const KState fw = gs.fwd(blockIdx.x), bw = gs.bwd(blockIdx.x);
+  Cn += (size_t)blockIdx.x * 2 * kGradMaxM * kGradMaxM * kGaussNodes;
+  Ct += (size_t)blockIdx.x * 2 * kGradMaxM * kGradMaxM;
   const int e = threadIdx.x, c = e / kGradMaxM, d = e % kGradMaxM;
   const int muf = fw.mused[0], mub = bw.mused[0];
   const bool ok = fw.status[0] == QK_OK && bw.status[0] == QK_OK && c < mub && d < muf;
@@ -147,7 +177,11 @@ k_grad_coeffs(KState fw, KState bw, const double* __restrict__ Cn, double* __res
 //     across lanes.
 // Lane i then adds s_n over the tile's positions whose state has bit i set,
 // every lane the total; per block the four waves' sums are added in wave
-// order into 2(L_max + 1) partial sums.
+// order into 2(L_max + 1) partial sums, and to those of the launches before
+// (the gradient is the sum over the steps).
+// Row y of the grid takes step y of gs: a step of a small sector has too few
+// tiles for its prologue and its ramp (the 20-site ring, 50 steps: 55 us each,
+// 8 us less in all kernels of the contraction).
 constexpr int kGradQ = 2 * (QK_MAX_L + 1);
 constexpr int kGcWaves = 4;                    // wavefronts per block
 constexpr int kGcN = 16;                       // positions per wavefront tile
@@ -186,15 +220,20 @@ __device__ __forceinline__ S gc_ld(const S* p) {
 
 template <typename S>
 __global__ void __launch_bounds__(256, 4)
-k_grad_contract(const S* __restrict__ states, uint64_t niter, int L, const double2* __restrict__ psi_k,
-                const double2* __restrict__ Uf, const double2* __restrict__ vm0, const double2* __restrict__ Ub,
-                size_t stride, const uint32_t* __restrict__ line_r0, const uint8_t* __restrict__ line_n, int pe,
-                KState fw, KState bw, const double* __restrict__ Ct, double* __restrict__ part) {
+k_grad_contract(const S* __restrict__ states, uint64_t niter, int L, GradSteps gs, size_t stride,
+                const uint32_t* __restrict__ line_r0, const uint8_t* __restrict__ line_n, int pe,
+                const double* __restrict__ Ct, double* __restrict__ part) {
   // niter positions of the workspace vectors (stride elements each): rows of
   // the sorted basis, or, with line tables, elements of the padded layout
   // whose row comes from their line's entry (unused padding is skipped)
   __shared__ double Af[kGcFrag];                // [M-block][K-step][lane]
   __shared__ double red[kGcWaves][kGradQ];
+  const size_t y = blockIdx.y;
+  const double2* __restrict__ psi_k = gs.psi - y * gs.D;
+  const double2* __restrict__ vm0 = gs.vm + y * gs.D;
+  const double2* __restrict__ Uf = gs.Uf - y * gs.basis;
+  const double2* __restrict__ Ub = gs.Ub + y * gs.basis;
+  Ct += y * 2 * kGradMaxM * kGradMaxM;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   // R in fragment order: lane l of (b, k) holds the R entry of output row
   // i = l % 16 (component (i / 4) % 2 of t_c, c = 8b + 2(i % 4) + i / 8) and
@@ -206,8 +245,8 @@ k_grad_contract(const S* __restrict__ states, uint64_t niter, int L, const doubl
     const double cr = Ct[2 * (c * kGradMaxM + d)], ci = Ct[2 * (c * kGradMaxM + d) + 1];
     Af[e] = pc == pd ? cr : (pc == 0 ? -ci : ci);
   }
-  const int muf = fw.mused[0] < kGradMaxM ? fw.mused[0] : kGradMaxM;
-  const int mub = bw.mused[0] < kGradMaxM ? bw.mused[0] : kGradMaxM;
+  const int muf = min(gs.fwd((int)y).mused[0], kGradMaxM);
+  const int mub = min(gs.bwd((int)y).mused[0], kGradMaxM);
   __syncthreads();
   const int q = lane >> 4, n = lane & 15;
   // row and validity of position p
@@ -303,39 +342,26 @@ k_grad_contract(const S* __restrict__ states, uint64_t niter, int L, const doubl
   if (tid < kGradQ) {
     double v = red[0][tid];
     for (int k = 1; k < kGcWaves; ++k) v += red[k][tid];
-    part[(size_t)blockIdx.x * kGradQ + tid] = v;
+    part[(y * gridDim.x + blockIdx.x) * kGradQ + tid] += v;
   }
 }
 
-// dA[i] += -i (S_i - S_total / 2), the partial sums of the G contraction
-// blocks totalled in a fixed order: kAccLanes lanes per column each add every
-// kAccLanes-th block, then one thread adds the lanes in order.
-constexpr int kAccLanes = 7;
-constexpr int kAccThreads = 1024;
-static_assert(kGradQ * kAccLanes <= kAccThreads, "one lane group per column");
-__global__ void __launch_bounds__(kAccThreads) k_grad_accum(const double* __restrict__ part, int G, int L,
-                                                           double* __restrict__ dA) {
-  __shared__ double red[kGradQ * kAccLanes];
-  __shared__ double tot[kGradQ];
-  const int t = threadIdx.x, c = t / kAccLanes, l = t % kAccLanes;
-  if (c < kGradQ) {
-    double acc = 0.0;
-    for (int g = l; g < G; g += kAccLanes) acc += part[(size_t)g * kGradQ + c];
-    red[c * kAccLanes + l] = acc;
+// Totals of the n rows of partial sums in a fixed order: kAccLanes lanes per
+// column each add every kAccLanes-th row, then the lanes are added pairwise.
+constexpr int kAccCols = 8, kAccLanes = 128;
+__global__ void __launch_bounds__(kAccCols * kAccLanes)
+k_grad_total(const double* __restrict__ part, int n, double* __restrict__ tot) {
+  __shared__ double red[kAccLanes][kAccCols];
+  const int c = threadIdx.x % kAccCols, l = threadIdx.x / kAccCols, col = blockIdx.x * kAccCols + c;
+  double acc = 0.0;
+  if (col < kGradQ)
+    for (int g = l; g < n; g += kAccLanes) acc += part[(size_t)g * kGradQ + col];
+  red[l][c] = acc;
+  for (int h = kAccLanes / 2; h > 0; h >>= 1) {
+    __syncthreads();
+    if (l < h) red[l][c] += red[l + h][c];
   }
-  __syncthreads();
-  if (t < kGradQ) {
-    double s = 0.0;
-    for (int k = 0; k < kAccLanes; ++k) s += red[t * kAccLanes + k];
-    tot[t] = s;
-  }
-  __syncthreads();
-  if (t < L) {
-    const double gr = tot[2 * t] - 0.5 * tot[2 * QK_MAX_L];
-    const double gi = tot[2 * t + 1] - 0.5 * tot[2 * QK_MAX_L + 1];
-    dA[2 * t] += gi;       // -i (gr + i gi) = gi - i gr
-    dA[2 * t + 1] -= gr;
-  }
+  if (l == 0 && col < kGradQ) tot[col] = red[0][c];
 }
 
 __global__ void k_basis_vector(double2* __restrict__ v, uint32_t D, uint32_t r0) {
@@ -350,7 +376,10 @@ qk_status grad_return_prob(qk_krylov* k, int64_t r0, double T, int n_steps, int 
   const int L = H->basis->L;
   const double dt = T / n_steps;
   const size_t vbytes = sizeof(double2) * (size_t)D;
-  const int G = 1024;
+  // steps of one launch of the contraction and its blocks for each: a wave
+  // takes eight tiles where that leaves 1024 blocks, and a block all there are
+  // at most (the rule of both ways below, which give the same bits)
+  const int S = std::min(n_steps, kGradSteps);
   // Every forward Krylov basis (and its coefficients) is kept for the
   // duration of the call when all of them fit in 80 % of the free device
   // memory, so the backward pass needs no rebuilding; QK_GRAD_KEEP=0 turns
@@ -392,7 +421,7 @@ qk_status grad_return_prob(qk_krylov* k, int64_t r0, double T, int n_steps, int 
   double2* cur = nullptr;    // running forward state
   double2* mir = nullptr;    // psi_{K-1-t} of the mirrored steps
   double2* mnext = nullptr;  // the state after it
-  double *Ct = nullptr, *Cn = nullptr, *part = nullptr, *dA = nullptr;
+  double *Ct = nullptr, *Cn = nullptr, *part = nullptr, *tot = nullptr;
   qk_status st = keep ? QK_OK : krylov_create(H, k->m, QK_C128, k->reorth, k->al, &kb);
   if (st != QK_OK) {
     dev_free(k->al, ubank);
@@ -411,13 +440,10 @@ qk_status grad_return_prob(qk_krylov* k, int64_t r0, double T, int n_steps, int 
   if (e == hipSuccess) e = dev_alloc(k->al, (void**)&cur, vbytes);
   if (e == hipSuccess && !keep) e = dev_alloc(k->al, (void**)&mir, vbytes);
   if (e == hipSuccess && !keep) e = dev_alloc(k->al, (void**)&mnext, vbytes);
-  if (e == hipSuccess) e = dev_alloc(k->al, (void**)&Ct, sizeof(double) * 2 * kGradMaxM * kGradMaxM);
-  if (e == hipSuccess) e = dev_alloc(k->al, (void**)&Cn, sizeof(double) * 2 * kGradMaxM * kGradMaxM * kGaussNodes);
-  if (e == hipSuccess) e = dev_alloc(k->al, (void**)&part, sizeof(double) * (size_t)G * kGradQ);
-  if (e == hipSuccess) e = dev_alloc(k->al, (void**)&dA, sizeof(double) * 2 * L);
-  if (e == hipSuccess) e = hipMemsetAsync(dA, 0, sizeof(double) * 2 * L, s);
-  const KState fw = make_kstate(k);
-  const KState bw = kb ? make_kstate(kb) : fw;
+  const int at_once = keep ? S : 1;   // steps whose bases are there together
+  if (e == hipSuccess) e = dev_alloc(k->al, (void**)&Ct, sizeof(double) * 2 * kGradMaxM * kGradMaxM * at_once);
+  if (e == hipSuccess)
+    e = dev_alloc(k->al, (void**)&Cn, sizeof(double) * 2 * kGradMaxM * kGradMaxM * kGaussNodes * at_once);
   // the workspaces' vectors in the padded layout of the two-pass split: the
   // contraction walks that layout and finds each element's row in its line
   const uint32_t* lr0 = nullptr;
@@ -429,6 +455,14 @@ qk_status grad_return_prob(qk_krylov* k, int64_t r0, double T, int n_steps, int 
     st = QK_EUNSUPPORTED;
   }
   if (st == QK_OK && k->d_Z) st = split_line_tables(H, QK_C128, &lr0, &lnn, &niter, &pe);
+  const uint64_t tiles = (niter + kGcN - 1) / kGcN;
+  const int G = (int)std::min<uint64_t>(
+      1024, std::max<uint64_t>(std::min<uint64_t>((tiles + kGcWaves - 1) / kGcWaves, (uint64_t)(1024 + S - 1) / S),
+                               tiles / (8 * kGcWaves)));
+  const size_t pbytes = sizeof(double) * (size_t)S * G * kGradQ;
+  if (e == hipSuccess) e = dev_alloc(k->al, (void**)&part, pbytes);
+  if (e == hipSuccess) e = dev_alloc(k->al, (void**)&tot, sizeof(double) * kGradQ);
+  if (e == hipSuccess) e = hipMemsetAsync(part, 0, pbytes, s);
   const GaussRule gr = gauss_legendre();
   auto chk = [&](const char* what) {
     if (st == QK_OK && e == hipSuccess) e = hipGetLastError();
@@ -445,22 +479,32 @@ qk_status grad_return_prob(qk_krylov* k, int64_t r0, double T, int n_steps, int 
     chk("checkpoint copy");
   }
   void* const u_home = k->d_U;
+  double* const c_home = k->d_coef;
+  int32_t* const i_home = k->d_int;
   for (int t = 0; t < n_steps && st == QK_OK; ++t) {
-    // with kept bases the step builds its basis directly in the bank
-    if (keep) k->d_U = (char*)ubank + (size_t)t * ubytes;
+    // with kept bases the step builds its basis and coefficients directly in
+    // the banks
+    if (keep) {
+      k->d_U = (char*)ubank + (size_t)t * ubytes;
+      k->d_coef = cbank + (size_t)t * cdoubles;
+      k->d_int = ibank + 2 * (size_t)t;
+    }
     st = launch_krylov_step(k, cur, dt, s);
     k->d_U = u_home;
-    if (st == QK_OK && keep) {
-      e = hipMemcpyAsync(cbank + (size_t)t * cdoubles, k->d_coef, sizeof(double) * cdoubles, hipMemcpyDeviceToDevice,
-                         s);
-      if (e == hipSuccess)
-        e = hipMemcpyAsync(ibank + 2 * (size_t)t, k->d_int, sizeof(int32_t) * 2, hipMemcpyDeviceToDevice, s);
-      chk("basis bank copy");
-    }
+    k->d_coef = c_home;
+    k->d_int = i_home;
     if (st == QK_OK && (t + 1) % c == 0 && (t + 1) / c < nck) {
       e = hipMemcpyAsync(ck + (size_t)((t + 1) / c) * D, cur, vbytes, hipMemcpyDeviceToDevice, s);
       chk("checkpoint copy");
     }
+  }
+  if (st == QK_OK && keep) {
+    // the workspace's coefficients are those of the last step
+    e = hipMemcpyAsync(c_home, cbank + (size_t)(n_steps - 1) * cdoubles, sizeof(double) * cdoubles,
+                       hipMemcpyDeviceToDevice, s);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(i_home, ibank + 2 * (size_t)(n_steps - 1), sizeof(int32_t) * 2, hipMemcpyDeviceToDevice, s);
+    chk("last step's coefficients");
   }
   double2 A = make_double2(0.0, 0.0);
   if (st == QK_OK) {
@@ -477,7 +521,42 @@ qk_status grad_return_prob(qk_krylov* k, int64_t r0, double T, int n_steps, int 
     hipLaunchKernelGGL(k_basis_vector, dim3((D + 255) / 256), dim3(256), 0, s, mir, D, (uint32_t)r0);
     chk("k_basis_vector");
   }
-  for (int t = n_steps - 1; t >= 0 && st == QK_OK; --t) {
+  // steps t, t - 1, ..., t - ny + 1: coefficients and contraction
+  auto contract = [&](const GradSteps& gs, int y0, int ny) {
+    double* const rows = part + (size_t)y0 * G * kGradQ;
+    hipLaunchKernelGGL(k_grad_nodes, dim3(kGaussNodes, ny), dim3(64), 0, s, gs, dt, gr, Cn);
+    chk("k_grad_nodes");
+    if (st != QK_OK) return;
+    hipLaunchKernelGGL(k_grad_coeffs, dim3(ny), dim3(kGradMaxM * kGradMaxM), 0, s, gs, (const double*)Cn, Ct);
+    chk("k_grad_coeffs");
+    if (st != QK_OK) return;
+    if (H->basis->wide)
+      hipLaunchKernelGGL(k_grad_contract<uint64_t>, dim3(G, ny), dim3(256), 0, s, (const uint64_t*)H->basis->d_states,
+                         niter, L, gs, (size_t)k->ustride, lr0, lnn, pe, (const double*)Ct, rows);
+    else
+      hipLaunchKernelGGL(k_grad_contract<uint32_t>, dim3(G, ny), dim3(256), 0, s, (const uint32_t*)H->basis->d_states,
+                         niter, L, gs, (size_t)k->ustride, lr0, lnn, pe, (const double*)Ct, rows);
+    chk("k_grad_contract");
+  };
+  GradSteps gs{};
+  gs.D = D;
+  if (keep) {
+    // Krylov bases of psi_t and of the costate's steps, which start from
+    // lambda_{t+1} = conj(psi_{K-1-t}): the forward step of the mirrored index
+    gs.coef = cdoubles;
+    gs.basis = ubytes / sizeof(double2);
+    for (int t = n_steps - 1; t >= 0 && st == QK_OK; t -= S) {
+      const int tm = n_steps - 1 - t;
+      gs.fw = kstate_at(k, cbank + (size_t)t * cdoubles, ibank + 2 * (size_t)t);
+      gs.bw = kstate_at(k, cbank + (size_t)tm * cdoubles, ibank + 2 * (size_t)tm);
+      gs.psi = ck + (size_t)t * D;
+      gs.vm = ck + (size_t)tm * D;
+      gs.Uf = (const double2*)((char*)ubank + (size_t)t * ubytes);
+      gs.Ub = (const double2*)((char*)ubank + (size_t)tm * ubytes);
+      contract(gs, 0, std::min(S, t + 1));
+    }
+  }
+  for (int t = n_steps - 1; t >= 0 && st == QK_OK && !keep; --t) {
     if (t % c == c - 1 || t == n_steps - 1) {
       // entering a segment from its end: recompute its states after the checkpoint
       const int t0 = (t / c) * c;
@@ -488,54 +567,42 @@ qk_status grad_return_prob(qk_krylov* k, int64_t r0, double T, int n_steps, int 
       }
       if (st != QK_OK) break;
     }
-    // Krylov basis of psi_t: kept from the forward pass, or rebuilt from the
-    // stored state (which is left unchanged)
-    const double2* Uf = keep ? (const double2*)((char*)ubank + (size_t)t * ubytes) : (const double2*)k->d_U;
-    const KState fwt = keep ? kstate_at(k, cbank + (size_t)t * cdoubles, ibank + 2 * (size_t)t) : fw;
-    if (!keep) st = launch_krylov_step(k, state_at(t), dt, s, StepUpTo::basis);
+    // Krylov basis of psi_t, rebuilt from the stored state (which is left
+    // unchanged), and of the mirrored step, taken by the second workspace from
+    // the mirrored state (which advances to the next)
+    st = launch_krylov_step(k, state_at(t), dt, s, StepUpTo::basis);
     if (st != QK_OK) break;
-    // the costate's step from lambda_{t+1} = conj(psi_{K-1-t}): the forward
-    // step of the mirrored index, kept from the forward pass or taken now by
-    // the second workspace from the mirrored state (which advances to the next)
-    const int tm = n_steps - 1 - t;
-    const double2* vm0 = keep ? ck + (size_t)tm * D : mir;
-    const double2* Ub = keep ? (const double2*)((char*)ubank + (size_t)tm * ubytes) : (const double2*)kb->d_U;
-    const KState bwt = keep ? kstate_at(k, cbank + (size_t)tm * cdoubles, ibank + 2 * (size_t)tm) : bw;
-    if (!keep) {
-      e = hipMemcpyAsync(mnext, mir, vbytes, hipMemcpyDeviceToDevice, s);
-      chk("mirrored state copy");
-      if (st == QK_OK) st = launch_krylov_step(kb, mnext, dt, s);
-      if (st != QK_OK) break;
-    }
-    hipLaunchKernelGGL(k_grad_nodes, dim3(kGaussNodes), dim3(64), 0, s, fwt, bwt, dt, gr, Cn);
-    chk("k_grad_nodes");
+    e = hipMemcpyAsync(mnext, mir, vbytes, hipMemcpyDeviceToDevice, s);
+    chk("mirrored state copy");
+    if (st == QK_OK) st = launch_krylov_step(kb, mnext, dt, s);
     if (st != QK_OK) break;
-    hipLaunchKernelGGL(k_grad_coeffs, dim3(1), dim3(kGradMaxM * kGradMaxM), 0, s, fwt, bwt, (const double*)Cn, Ct);
-    chk("k_grad_coeffs");
-    if (st != QK_OK) break;
-    if (H->basis->wide)
-      hipLaunchKernelGGL(k_grad_contract<uint64_t>, dim3(G), dim3(256), 0, s, (const uint64_t*)H->basis->d_states,
-                         niter, L, (const double2*)state_at(t), Uf, vm0, Ub, (size_t)k->ustride, lr0, lnn, pe, fwt,
-                         bwt, Ct, part);
-    else
-      hipLaunchKernelGGL(k_grad_contract<uint32_t>, dim3(G), dim3(256), 0, s, (const uint32_t*)H->basis->d_states,
-                         niter, L, (const double2*)state_at(t), Uf, vm0, Ub, (size_t)k->ustride, lr0, lnn, pe, fwt,
-                         bwt, Ct, part);
-    chk("k_grad_contract");
-    if (st != QK_OK) break;
-    hipLaunchKernelGGL(k_grad_accum, dim3(1), dim3(kAccThreads), 0, s, part, G, L, dA);
-    chk("k_grad_accum");
-    if (!keep) std::swap(mir, mnext);
+    gs.fw = make_kstate(k);
+    gs.bw = make_kstate(kb);
+    gs.psi = state_at(t);
+    gs.vm = mir;
+    gs.Uf = (const double2*)k->d_U;
+    gs.Ub = (const double2*)kb->d_U;
+    contract(gs, (n_steps - 1 - t) % S, 1);
+    std::swap(mir, mnext);
   }
-  std::vector<double> dAh(2 * L);
+  std::vector<double> th(kGradQ);
   if (st == QK_OK) {
-    e = hipMemcpyAsync(dAh.data(), dA, sizeof(double) * 2 * L, hipMemcpyDeviceToHost, s);
+    hipLaunchKernelGGL(k_grad_total, dim3((kGradQ + kAccCols - 1) / kAccCols), dim3(kAccCols * kAccLanes), 0, s,
+                       (const double*)part, S * G, tot);
+    chk("k_grad_total");
+  }
+  if (st == QK_OK) {
+    e = hipMemcpyAsync(th.data(), tot, sizeof(double) * kGradQ, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) st = hip_fail(e, "qk_grad_return_prob readback");
   }
   if (st == QK_OK) {
     *F = A.x * A.x + A.y * A.y;
-    for (int i = 0; i < L; ++i) dFdh[i] = 2.0 * (A.x * dAh[2 * i] + A.y * dAh[2 * i + 1]);
+    for (int i = 0; i < L; ++i) {
+      // dA_i = -i (S_i - S_total / 2)
+      const double gr_ = th[2 * i] - 0.5 * th[2 * QK_MAX_L], gi = th[2 * i + 1] - 0.5 * th[2 * QK_MAX_L + 1];
+      dFdh[i] = 2.0 * (A.x * gi - A.y * gr_);
+    }
   }
   (void)hipStreamSynchronize(s);
   dev_free(k->al, ck);
@@ -546,7 +613,7 @@ qk_status grad_return_prob(qk_krylov* k, int64_t r0, double T, int n_steps, int 
   dev_free(k->al, Ct);
   dev_free(k->al, Cn);
   dev_free(k->al, part);
-  dev_free(k->al, dA);
+  dev_free(k->al, tot);
   dev_free(k->al, ubank);
   dev_free(k->al, cbank);
   dev_free(k->al, ibank);

@@ -487,8 +487,9 @@ QK_API qk_status qk_krylov_evolve(qk_krylov* k, void* psi, double t, const qk_ad
   hipStream_t s = (hipStream_t)stream;
   const int B = k->batch;
   const KState ks = make_kstate(k);
-  std::vector<double> tau(2 * B);
-  std::vector<int32_t> iv(2 * B);
+  // one copy a step: error estimates, accepted and suggested steps lie together
+  std::vector<double> res(3 * B);
+  const double *err = res.data(), *tau = err + B;
   double done = 0.0, dt_try = p->dt_init, err_sum = 0.0, dmin = INFINITY, dmax = 0.0;
   int steps = 0;
   while (t - done > 1e-14 * t) {
@@ -499,13 +500,11 @@ QK_API qk_status qk_krylov_evolve(qk_krylov* k, void* psi, double t, const qk_ad
     double tau_max = std::min(std::min(dt_try, p->dt_max), t - done);
     st = launch_krylov_adaptive_step(k, psi, tau_max, p->tol, s);
     if (st != QK_OK) return st;
-    QK_HIP(hipMemcpyAsync(tau.data(), ks.tau, sizeof(double) * 2 * B, hipMemcpyDeviceToHost, s));
-    QK_HIP(hipMemcpyAsync(iv.data(), k->d_int, sizeof(int32_t) * 2 * B, hipMemcpyDeviceToHost, s));
-    double e0 = 0.0;
-    QK_HIP(hipMemcpyAsync(&e0, ks.err, sizeof(double), hipMemcpyDeviceToHost, s));
+    QK_HIP(hipMemcpyAsync(res.data(), ks.err, sizeof(double) * 3 * B, hipMemcpyDeviceToHost, s));
     QK_HIP(hipStreamSynchronize(s));
+    const double e0 = err[0];
     for (int b = 0; b < B; ++b)
-      if (iv[B + b] != QK_OK) {
+      if (std::isnan(tau[B + b])) {
         set_error("non-finite Lanczos coefficient");
         return QK_ENUMERIC;
       }

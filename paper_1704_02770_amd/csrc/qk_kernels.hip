@@ -221,7 +221,7 @@ k_small_expm(KState st, int m, int B, double tau, const double* __restrict__ tau
 
 
 // Step size of column b by one wave: st.tau[b] = accepted step, st.tau[B + b] =
-// suggested next step.  A recurrence that stopped early spans an invariant
+// suggested next step (not a number if its status is not QK_OK).  A recurrence that stopped early spans an invariant
 // subspace and accepts tau_max.
 __global__ void __launch_bounds__(64)
 k_step_size(KState st, int m, int B, double tau_max, double tol, const double* __restrict__ partB, int Gp) {
@@ -229,7 +229,7 @@ k_step_size(KState st, int m, int B, double tau_max, double tol, const double* _
   const int i = threadIdx.x;
   const double beta_last = last_residual_norm(partB, Gp, B, b, i);
   const int mu = st.mused[b];
-  double tau = tau_max, next = tau_max;
+  double tau = tau_max, next = st.status[b] == QK_OK ? tau_max : NAN;   // NaN: the column has failed
   if (st.status[b] == QK_OK && mu == m && m > 1)
     tau = step_size(tri_lane(st, B, b, mu, i), m, i, st.n0[b] * beta_last, tau_max, tol, next);
   if (i == 0) {

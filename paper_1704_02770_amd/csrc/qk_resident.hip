@@ -345,7 +345,7 @@ __device__ __forceinline__ void res_coefs(ResShared& sh, const ResArgs& ra, cons
   double tau = ra.tau;
   if (ra.tail == kTailAdaptive) {
     for (int b = wave; b < B; b += waves) {
-      double next = ra.tau, own = ra.tau;
+      double next = sh.ok[b] ? ra.tau : NAN, own = ra.tau;
       if (sh.ok[b] && sh.mu[b] == m && m > 1) own = step_size(tri(b, m), m, lane, sh.n0[b] * sh.last[b], ra.tau, ra.tol, next);
       if (lane == 0) {
         sh.sa[b] = own;
@@ -447,6 +447,7 @@ __device__ __forceinline__ void res_alpha(ResShared& sh, const ResArgs& ra, cons
       if (!(n0 > 0.0)) {
         active = 0;   // zero vector: nothing to propagate
         sh.mu[b] = 0;
+        if (!isfinite(S2)) sh.ok[b] = 0;
         if (first) {
           st.mused[b] = 0;
           if (!isfinite(S2)) st.status[b] = QK_ENUMERIC;

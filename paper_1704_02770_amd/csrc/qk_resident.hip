@@ -68,7 +68,8 @@ constexpr uint32_t kClosed = 0x80000000u;
 enum { kTailNone = 0, kTailStep = 1, kTailAdaptive = 2 };
 
 struct ResArgs {
-  int L, pbc, B, lbp, m, nbonds;
+  int L, pbc, B, lbp, m, nbonds, reorth;
+  int qcap;                        // quantities of a slot of words
   uint32_t D;
   int groups;                      // work-groups that the rows take
   int join_max;                    // work-groups that may register (all of them, or fewer in tests)
@@ -77,7 +78,7 @@ struct ResArgs {
   const uint32_t* bn;
   const double* fields;
   uint64_t stride;                 // elements of a basis slot
-  uint64_t* words;                 // [2][groups][2][lanes per row] pairs of words
+  uint64_t* words;                 // [2][groups][2, reorth: 4][lanes per row] pairs of words
   ResCtl* ctl;
   int tail;                        // what follows the recurrence (kTail*)
   double* norm2;                   // [B] |u_m|^2
@@ -121,8 +122,8 @@ __device__ __forceinline__ void word_st(uint64_t* p, uint64_t v) {
 }
 
 struct ResShared {
-  double red[2 * kResMaxThreads / 64 * kResMaxLanes];
-  double sa[kResMaxLanes], sb[kResMaxLanes], sc[kResMaxLanes], sd[kResMaxLanes];
+  double red[4 * kResMaxThreads / 64 * kResMaxLanes];
+  double sa[kResMaxLanes], sb[kResMaxLanes], sc[kResMaxLanes], sd[kResMaxLanes], ser[kResMaxLanes], sei[kResMaxLanes];
   int act[kResMaxLanes];
   // per column: coefficients and scales, then the combination's coefficients in al and be
   double al[kResMaxLanes * 64], be[kResMaxLanes * 64], sg[kResMaxLanes * 64];
@@ -182,7 +183,7 @@ __device__ __forceinline__ void res_publish(ResShared& sh, const ResArgs& ra, in
     double t = 0.0;
     for (int w = 0; w < waves; ++w) t += sh.red[(q * waves + w) * Bp + p];
     const uint64_t b = __builtin_bit_cast(uint64_t, t), tag = (uint64_t)no << 32;
-    uint64_t* w = ra.words + (((size_t)(no & 1u) * nslots + slot) * (size_t)(2 * Bp) + (size_t)tid) * 2;
+    uint64_t* w = ra.words + (((size_t)(no & 1u) * nslots + slot) * (size_t)ra.qcap * Bp + (size_t)tid) * 2;
     word_st(w, tag | (uint32_t)b);
     word_st(w + 1, tag | (b >> 32));
   }
@@ -193,7 +194,7 @@ __device__ __forceinline__ void res_publish(ResShared& sh, const ResArgs& ra, in
 __device__ __forceinline__ double res_collect(ResShared& sh, const ResArgs& ra, int Q, uint32_t no, uint32_t nslots) {
   const int Bp = 1 << ra.lbp, cols = Q * Bp, lane = threadIdx.x;
   const uint32_t n = nslots * (uint32_t)cols;
-  const uint64_t* base = ra.words + (size_t)(no & 1u) * nslots * (size_t)(2 * Bp) * 2;
+  const uint64_t* base = ra.words + (size_t)(no & 1u) * nslots * (size_t)ra.qcap * Bp * 2;
   // lane l adds the entries l, l + 64, ..., four at a time, then the lanes of a
   // column are added in a fixed order
   double acc = 0.0;
@@ -207,7 +208,7 @@ __device__ __forceinline__ double res_collect(ResShared& sh, const ResArgs& ra, 
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const uint32_t i = i0 + 64u * e + (uint32_t)lane, slot = i / (uint32_t)cols, c = i & (uint32_t)(cols - 1);
-        const uint64_t* w = base + ((size_t)(i < n ? slot : 0u) * (2 * Bp) + c) * 2;
+        const uint64_t* w = base + ((size_t)(i < n ? slot : 0u) * (ra.qcap * Bp) + c) * 2;
         a[e] = word_ld(w);
         b[e] = word_ld(w + 1);
       }
@@ -407,7 +408,20 @@ __device__ __forceinline__ void res_combine(const ResShared& sh, const ResArgs& 
   psi[i] = V{(T)ar, (T)ai};
 }
 
-// u_{j+1} of one row, as the update pass forms it.
+// u_{j+1} of one row, as the update pass forms it; with the component along
+// v_{j-1} taken out (er, ei: <v_{j-1}, w> sigma_{j-1}).
+template <typename T>
+__device__ __forceinline__ typename Cx<T>::V res_next(double c, double d, double er, double ei, typename Cx<T>::V w,
+                                                      typename Cx<T>::V u, typename Cx<T>::V um) {
+  double nx = c * ((double)w.x - d * (double)u.x);
+  double ny = c * ((double)w.y - d * (double)u.y);
+  nx -= er * (double)um.x - ei * (double)um.y;
+  ny -= er * (double)um.y + ei * (double)um.x;
+  typename Cx<T>::V o;
+  o.x = (T)nx;
+  o.y = (T)ny;
+  return o;
+}
 template <typename T>
 __device__ __forceinline__ typename Cx<T>::V res_next(double c, double d, typename Cx<T>::V w, typename Cx<T>::V u) {
   typename Cx<T>::V o;
@@ -418,7 +432,8 @@ __device__ __forceinline__ typename Cx<T>::V res_next(double c, double d, typena
 
 // What lane b < B of the first wave keeps of column b over the iterations.
 struct ResCol {
-  double sigma = 0.0, smax = 0.0, alpha = 0.0;   // sigma_j, the largest coefficient so far, alpha_j
+  double sigma = 0.0, before = 0.0;              // sigma_j, sigma_{j-1}
+  double smax = 0.0, alpha = 0.0;                // the largest coefficient so far, alpha_j
 };
 
 // By the first wave, after exchange A of iteration j (lane q * Bp + b holds S_q
@@ -427,7 +442,8 @@ struct ResCol {
 __device__ __forceinline__ void res_alpha(ResShared& sh, const ResArgs& ra, const KState& st, int j, bool first,
                                           double S, ResCol& col) {
   const int b = threadIdx.x, B = ra.B, Bp = 1 << ra.lbp;
-  const double S2 = j == 0 ? __shfl(S, b + Bp) : 0.0;
+  // second and third quantity: |u_0|^2, or <u_{j-1}, w> to reorthogonalise
+  const double S2 = __shfl(S, (b + Bp) & 63), S3 = __shfl(S, (b + 2 * Bp) & 63);
   if (b >= B) return;
   int active = sh.act[b];
   if (active) {
@@ -457,6 +473,8 @@ __device__ __forceinline__ void res_alpha(ResShared& sh, const ResArgs& ra, cons
       col.alpha = col.sigma * S;
       c = 1.0;
       d = col.alpha * col.sigma;
+      sh.ser[b] = col.before * col.before * S2;
+      sh.sei[b] = col.before * col.before * S3;
     }
     if (active && !isfinite(col.alpha)) {
       active = 0;
@@ -507,6 +525,7 @@ __device__ __forceinline__ void res_beta(ResShared& sh, const ResArgs& ra, const
       if (active) {
         sh.sa[b] = 1.0 / beta;
         sh.sb[b] = beta * col.sigma;
+        col.before = col.sigma;
         col.sigma = 1.0 / beta;
         sh.sg[b * 64 + j + 1] = col.sigma;
         if (first) st.sigma[(j + 1) * B + b] = col.sigma;
@@ -540,7 +559,11 @@ constexpr bool resident_tail = !(NT > 512 && std::is_same<T, double>::value);
 // Loads of LOADS neighbours are in flight at a time, as many as the registers of
 // a thread hold beside everything else: all of them with two waves a SIMD
 // (L = 18: 3.7 us an iteration in three batches, 1.2 at once), seven with three.
-template <typename T, int KMAX, int OLO, int NT, int LOADS>
+// LATE: u_{j+1} itself is published, with the second exchange, and gathered
+// after it.  Local reorthogonalisation takes it: the other form would need
+// u_{j-1} at the neighbours as well.  The gather no longer runs beside the
+// exchange (L = 20, 330 against 410 us a step), so nothing else does.
+template <typename T, int KMAX, int OLO, int NT, int LOADS, bool LATE>
 __global__ void __launch_bounds__(NT, NT / 256)
 k_resident(ResArgs ra, typename Cx<T>::V* psi, typename Cx<T>::V* U, typename Cx<T>::V* X, KState st) {
   using V = typename Cx<T>::V;
@@ -635,34 +658,42 @@ k_resident(ResArgs ra, typename Cx<T>::V* psi, typename Cx<T>::V* U, typename Cx
         for (int k = 0; k < KMAX; ++k) sum.add(k, un[k]);
         const V w = res_w<T, OLO>(d, g, ca, cb, u, um, sum.total());
         const ResBuf<V> bx(X + (size_t)(j & 1) * nel, nel);
-        if (mine) bx.template st<kSc1>(eo, w);
+        const bool ro = LATE && ra.reorth && j > 0;
+        if (!LATE && mine) bx.template st<kSc1>(eo, w);
         const bool on = mine && has;
         const double s1 = on ? (double)u.x * (double)w.x + (double)u.y * (double)w.y : 0.0;
         if (j == 0) {
           const double v[2] = {s1, on ? (double)u.x * (double)u.x + (double)u.y * (double)u.y : 0.0};
-          res_partials<2, true>(sh, ra, v);
+          res_partials<2, !LATE>(sh, ra, v);
+        } else if (ro) {
+          const double v[4] = {s1, on ? (double)um.x * (double)w.x + (double)um.y * (double)w.y : 0.0,
+                               on ? (double)um.x * (double)w.y - (double)um.y * (double)w.x : 0.0, 0.0};
+          res_partials<4, false>(sh, ra, v);
         } else {
           const double v[1] = {s1};
-          res_partials<1, true>(sh, ra, v);
+          res_partials<1, !LATE>(sh, ra, v);
         }
         if (wave0) {
-          const int Q = j == 0 ? 2 : 1;
+          const int Q = j == 0 ? 2 : ro ? 4 : 1;
           res_publish(sh, ra, Q, no, G, ticket);
           res_alpha(sh, ra, st, j, first, res_collect(sh, ra, Q, no, G), col);
         }
         __syncthreads();
         const bool live = p < B && sh.act[p] != 0;
         const double c = live ? sh.sc[p] : 0.0, dd = live ? sh.sd[p] : 0.0;
-        const V o = res_next<T>(c, dd, w, u);
+        V o;
+        if (ro) o = res_next<T>(c, dd, live ? sh.ser[p] : 0.0, live ? sh.sei[p] : 0.0, w, u, um);
+        else o = res_next<T>(c, dd, w, u);
+        if (LATE && live && j + 1 < ra.m) bx.template st<kSc1>(eo, o);
         const double v[1] = {live && has ? (double)o.x * (double)o.x + (double)o.y * (double)o.y : 0.0};
-        res_partials<1, false>(sh, ra, v);
+        res_partials<1, LATE>(sh, ra, v);
         if (wave0) res_publish(sh, ra, 1, no + 1, G, ticket);
         if (j + 1 < ra.m) {
           if (live) ResBuf<V>(U + (size_t)j * ra.stride, nel).template st<0>(eo, o);
           // w at the neighbours, while the sums are under way
 #pragma unroll
-          for (int k0 = 0; k0 < KMAX; k0 += LOADS) {
-            V x[LOADS];
+          for (int k0 = 0; k0 < (LATE ? 0 : KMAX); k0 += LATE ? 1 : LOADS) {
+            V x[LATE ? 1 : LOADS];
 #pragma unroll
             for (int i = 0; i < LOADS; ++i)
               if (k0 + i < KMAX) x[i] = bx.template ld<kSc1>(LDSOFF ? lo[(k0 + i) * NT + tid] : off[LDSOFF ? 0 : k0 + i]);
@@ -681,6 +712,9 @@ k_resident(ResArgs ra, typename Cx<T>::V* psi, typename Cx<T>::V* U, typename Cx
         no += 2;
         __syncthreads();
         if (!sh.go) break;
+        if (LATE)
+#pragma unroll
+          for (int k = 0; k < KMAX; ++k) un[k] = bx.template ld<kSc1>(LDSOFF ? lo[k * NT + tid] : off[LDSOFF ? 0 : k]);
       }
     } else if (R != 0) {
       // rows of missing work-groups are dealt out: vectors in memory, agent scope
@@ -690,7 +724,8 @@ k_resident(ResArgs ra, typename Cx<T>::V* psi, typename Cx<T>::V* U, typename Cx
         const ResBuf<V> bx(X, nel), bo(U + (size_t)j * ra.stride, nel);
         const bool mine = p < B && sh.act[p] != 0;
         const T ca = mine ? (T)sh.sa[p] : (T)0, cb = mine ? (T)sh.sb[p] : (T)0;
-        const int Q = j == 0 ? 2 : 1;
+        const bool ro = LATE && ra.reorth && j > 0;
+        const int Q = j == 0 ? 2 : ro ? 4 : 1;
         for (uint32_t ch = ticket; ch < G; ch += R) {
           const uint32_t r = (ch * (uint32_t)nt + (uint32_t)tid) >> ra.lbp;
           const bool on = r < ra.D && mine;
@@ -705,9 +740,15 @@ k_resident(ResArgs ra, typename Cx<T>::V* psi, typename Cx<T>::V* U, typename Cx
           for (int k = 0; k < KMAX; ++k) sum.add(k, bu.template ld<kSc1>(lo[k * NT + tid]));
           const V w = res_w<T, OLO>(on ? res_diag(ra, s, f) : 0.0, g, ca, cb, x, xm, sum.total());
           bx.template st<kSc1>(e, w);
-          const double v[2] = {on ? (double)x.x * (double)w.x + (double)x.y * (double)w.y : 0.0,
-                               on ? (double)x.x * (double)x.x + (double)x.y * (double)x.y : 0.0};
-          res_partials<2, true>(sh, ra, v);
+          const double s1 = on ? (double)x.x * (double)w.x + (double)x.y * (double)w.y : 0.0;
+          if (ro) {
+            const double v[4] = {s1, on ? (double)xm.x * (double)w.x + (double)xm.y * (double)w.y : 0.0,
+                                 on ? (double)xm.x * (double)w.y - (double)xm.y * (double)w.x : 0.0, 0.0};
+            res_partials<4, true>(sh, ra, v);
+          } else {
+            const double v[2] = {s1, on ? (double)x.x * (double)x.x + (double)x.y * (double)x.y : 0.0};
+            res_partials<2, true>(sh, ra, v);
+          }
           if (wave0) res_publish(sh, ra, Q, no, G, ch);
           __syncthreads();
         }
@@ -719,7 +760,10 @@ k_resident(ResArgs ra, typename Cx<T>::V* psi, typename Cx<T>::V* U, typename Cx
           const uint32_t r = (ch * (uint32_t)nt + (uint32_t)tid) >> ra.lbp;
           const bool on = r < ra.D && live;
           const uint32_t e = on ? (r * (uint32_t)B + p) * (uint32_t)sizeof(V) : kNoRow;
-          const V o = res_next<T>(c, dd, bx.template ld<kSc1>(e), bu.template ld<kSc1>(e));
+          const V w = bx.template ld<kSc1>(e), x = bu.template ld<kSc1>(e);
+          V o;
+          if (ro) o = res_next<T>(c, dd, live ? sh.ser[p] : 0.0, live ? sh.sei[p] : 0.0, w, x, bm.template ld<kSc1>(e));
+          else o = res_next<T>(c, dd, w, x);
           if (j + 1 < ra.m) bo.template st<kSc1>(e, o);
           const double v[1] = {on ? (double)o.x * (double)o.x + (double)o.y * (double)o.y : 0.0};
           res_partials<1, true>(sh, ra, v);
@@ -766,7 +810,7 @@ k_resident_one(ResArgs ra, typename Cx<T>::V* psi, typename Cx<T>::V* U, KState 
   __shared__ ResShared sh;
   __shared__ uint32_t lo[KMAX * kOneThreads];
   __shared__ V ul[kOneThreads + 1];                        // u_j of the rows, and a zero
-  __shared__ double red[2][2 * kOneThreads / 64 * kResMaxLanes];   // of the two sums in turn
+  __shared__ double red[2][3 * kOneThreads / 64 * kResMaxLanes];   // of the two sums in turn
   const int tid = threadIdx.x, nt = blockDim.x, B = ra.B, Bp = 1 << ra.lbp, p = tid & (Bp - 1);
   const int lane = tid & 63, wave = tid >> 6, waves = nt >> 6;
   for (int i = tid; i < kBinomStride * kBinomStride; i += nt) sh.tab[i] = ra.bn[i];
@@ -816,7 +860,7 @@ k_resident_one(ResArgs ra, typename Cx<T>::V* psi, typename Cx<T>::V* U, KState 
   const bool rec = tid < B;   // records its column's results
   bool act = p < B, ok = true;
   int mu = ra.m;
-  double sa = 1.0, sb = 0.0, sigma = 0.0, smax = 0.0, n0 = 0.0, last = 0.0;
+  double sa = 1.0, sb = 0.0, sigma = 0.0, before = 0.0, smax = 0.0, n0 = 0.0, last = 0.0;
   for (int j = 0; j < ra.m; ++j) {
     const T ca = act ? (T)sa : (T)0, cb = act ? (T)sb : (T)0;
     HopSum<T, KMAX, OLO> sum;
@@ -829,6 +873,15 @@ k_resident_one(ResArgs ra, typename Cx<T>::V* psi, typename Cx<T>::V* U, KState 
     if (j == 0) {
       const double t2 = res_wave_sum(on ? (double)u.x * (double)u.x + (double)u.y * (double)u.y : 0.0, Bp);
       if (lane < Bp) red[0][(waves + wave) * Bp + lane] = t2;
+    }
+    const bool ro = ra.reorth && j > 0;
+    if (ro) {
+      const double t3r = res_wave_sum(on ? (double)um.x * (double)w.x + (double)um.y * (double)w.y : 0.0, Bp);
+      const double t3i = res_wave_sum(on ? (double)um.x * (double)w.y - (double)um.y * (double)w.x : 0.0, Bp);
+      if (lane < Bp) {
+        red[0][(waves + wave) * Bp + lane] = t3r;
+        red[0][(2 * waves + wave) * Bp + lane] = t3i;
+      }
     }
     __syncthreads();
     const double S = total(red[0]);
@@ -855,7 +908,13 @@ k_resident_one(ResArgs ra, typename Cx<T>::V* psi, typename Cx<T>::V* U, KState 
       mu = j;
     }
     const double sj = sigma;
-    const V o = act ? res_next<T>(c, dd, w, u) : V{0, 0};
+    V o = {0, 0};
+    if (ro) {
+      const double er = before * before * total(red[0] + waves * Bp), ei = before * before * total(red[0] + 2 * waves * Bp);
+      if (act) o = res_next<T>(c, dd, er, ei, w, u, um);
+    } else if (act) {
+      o = res_next<T>(c, dd, w, u);
+    }
     ul[tid] = o;
     if (act && has && j + 1 < ra.m) U[(size_t)j * ra.stride + e] = o;
     const double t3 = res_wave_sum(act && has ? (double)o.x * (double)o.x + (double)o.y * (double)o.y : 0.0, Bp);
@@ -883,6 +942,7 @@ k_resident_one(ResArgs ra, typename Cx<T>::V* psi, typename Cx<T>::V* U, KState 
       } else {
         sb = beta * sigma;
         sa = 1.0 / beta;
+        before = sigma;
         sigma = sa;
       }
     }
@@ -920,7 +980,7 @@ k_resident_one(ResArgs ra, typename Cx<T>::V* psi, typename Cx<T>::V* U, KState 
 // (that of the two-pass split has no d_res either).
 static uint64_t resident_lanes(const qk_krylov* k) {
   const qk_ham* H = k->H;
-  if (H->p.mode != QK_MATFREE || H->basis->L > kResMaxSites || k->reorth != 0) return 0;
+  if (H->p.mode != QK_MATFREE || H->basis->L > kResMaxSites || k->reorth > 1) return 0;
   uint64_t Bp = 1;
   while (Bp < (uint64_t)k->batch) Bp *= 2;
   const uint64_t lanes = (uint64_t)k->D * Bp;
@@ -950,7 +1010,7 @@ void resident_bytes(const qk_krylov* k, size_t* head, size_t* body) {
   const ResShape sp = resident_shape(lanes, per_row);
   *head = sizeof(ResCtl);
   if (sp.groups == 1) return;
-  *head += sizeof(uint64_t) * (size_t)2 * sp.groups * 2 * per_row * 2;
+  *head += sizeof(uint64_t) * (size_t)2 * sp.groups * (k->reorth ? 4 : 2) * per_row * 2;
   *body = (size_t)2 * k->D * k->batch * (k->dtype == QK_C128 ? 16 : 8);
 }
 
@@ -968,22 +1028,27 @@ struct ResLaunch {
   template <typename T, int KMAX, int OLO, int NT, int LOADS>
   void many() const {
     using V = typename Cx<T>::V;
-    hipLaunchKernelGGL((k_resident<T, KMAX, OLO, NT, LOADS>), dim3(sp.groups), dim3(sp.threads), 0, s, ra,
+    hipLaunchKernelGGL((k_resident<T, KMAX, OLO, NT, LOADS, LOADS == 0>), dim3(sp.groups), dim3(sp.threads), 0, s, ra,
                        (V*)psi, (V*)U, (V*)X, st);
   }
-  // the bonds that a thread keeps registers for: 14, 17 or 20
+  // the bonds that a thread keeps registers for: 14, 17 or 20; no loads beside
+  // the neighbours' values where they are gathered late
   template <typename T, int OLO>
   void go() const {
     constexpr int LOADS = std::is_same<T, double>::value ? 7 : 20;   // of the largest work-groups
+    const bool late = ra.reorth != 0;
     if (sp.groups == 1) {
       if (OLO == 0 && ra.nbonds <= 14) one<T, 14, 0>();
       else one<T, 20, OLO>();
     } else if (sp.threads <= 512) {
-      if (OLO == 0 && ra.nbonds <= 14) many<T, 14, 0, 512, 14>();
+      if (OLO == 0 && ra.nbonds <= 17 && late) many<T, 17, 0, 512, 0>();
+      else if (late) many<T, 20, OLO, 512, 0>();
+      else if (OLO == 0 && ra.nbonds <= 14) many<T, 14, 0, 512, 14>();
       else if (OLO == 0 && ra.nbonds <= 17) many<T, 17, 0, 512, 17>();
       else many<T, 20, OLO, 512, 20>();
     } else {
-      many<T, 20, OLO, kResMaxThreads, LOADS>();
+      if (late) many<T, 20, OLO, kResMaxThreads, 0>();
+      else many<T, 20, OLO, kResMaxThreads, LOADS>();
     }
   }
 };
@@ -1010,6 +1075,8 @@ qk_status launch_resident(qk_krylov* k, void* psi, double rtol, double tau, Step
   ra.B = k->batch;
   while ((1 << ra.lbp) < k->batch) ++ra.lbp;
   ra.m = k->m;
+  ra.reorth = k->reorth;
+  ra.qcap = k->reorth ? 4 : 2;
   ra.nbonds = ra.pbc ? ra.L : ra.L - 1;
   ra.D = (uint32_t)k->D;
   ra.groups = rl.sp.groups;

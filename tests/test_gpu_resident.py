@@ -20,9 +20,9 @@ CASES = [(2, 1, False, 1), (5, 4, True, 3), (8, 4, True, 1), (11, 5, False, 1), 
          (20, 10, True, 1)]
 
 
-def _workspace(L, N, pbc, Bn, dtype, m, mode=qk.QK_MATFREE):
+def _workspace(L, N, pbc, Bn, dtype, m, mode=qk.QK_MATFREE, reorth=0):
     hs = np.stack([random_fields(L, 900 + i) for i in range(Bn)])
-    return qk.qk_krylov_create(qk.qk_ham_create(qk.qk_basis_build(L, N), 1.0, 0.7, pbc, hs, mode), m, dtype)
+    return qk.qk_krylov_create(qk.qk_ham_create(qk.qk_basis_build(L, N), 1.0, 0.7, pbc, hs, mode), m, dtype, reorth=reorth)
 
 
 def _state(k, seed, dtype):
@@ -58,6 +58,26 @@ def test_one_launch_follows_the_passes(monkeypatch, L, N, pbc, Bn, dtype):
         say("resident, dealt out to", n)
         monkeypatch.setenv("QK_RESIDENT_JOIN", n)
         assert np.array_equal(_steps(_workspace(L, N, pbc, Bn, dtype, m), 5, dtype), one)
+
+
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
+@pytest.mark.parametrize("L,N,pbc,Bn", [(8, 4, True, 1), (11, 5, False, 2), (13, 6, True, 1), (14, 7, False, 8),
+                                        (16, 8, True, 3), (18, 9, True, 1), (19, 9, False, 1), (20, 10, True, 1)])
+def test_local_reorthogonalisation_follows_the_passes(monkeypatch, L, N, pbc, Bn, dtype):
+    m = 12
+    say("resident reorth", L, N, pbc, Bn, dtype)
+    k = _workspace(L, N, pbc, Bn, dtype, m, reorth=1)
+    one = _steps(k, 5, dtype)
+    plain = _steps(_workspace(L, N, pbc, Bn, dtype, m), 5, dtype)
+    qk.qk_krylov_profile(k, True)   # kernel by kernel
+    passes = _steps(k, 5, dtype)
+    # as above, and one more product and sum of every element
+    tol = 2 * m * 5 * EPS[dtype] * np.max(np.abs(passes))
+    assert np.max(np.abs(one - passes)) < tol
+    assert not np.array_equal(one, plain)   # it does something
+    say("resident reorth, dealt out")
+    monkeypatch.setenv("QK_RESIDENT_JOIN", "2")
+    assert np.array_equal(_steps(_workspace(L, N, pbc, Bn, dtype, m, reorth=1), 5, dtype), one)
 
 
 def test_columns_that_end_early():

@@ -17,7 +17,7 @@ complex128 chain from the Neel state to t = 100 with error-controlled steps
 reports its step count and wall time; `mixed` times the batched workload of
 64 phases of the L = 20 ring plus single rings of L = 16, 18, 20, 22 (h = 2,
 complex64, one hipGraph replay per step, and in the default launch shape the
-graph of one branch per workspace against use_graph = 2, which runs the same launches); `large` times Krylov steps of the
+use_graph = 1 against use_graph = 2, which runs the same launches); `large` times Krylov steps of the
 L = 30 ring (m = 20, dt = 0.05, complex128 and complex64).  Every rate is the
 median of --repeats timed runs of exactly --steps steps.  Also reported: standalone
 y = H x throughput (algorithmic bytes 2 s D per call), a device-copy ceiling,

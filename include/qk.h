@@ -367,14 +367,16 @@ qk_status qk_batch_items(const qk_batch* b, int32_t* items);
  * written to P_device[k * items + offset_i + item] (offsets in workspace
  * order).  use_graph selects how a step is launched:
  *   0  every kernel of every workspace enqueued directly;
- *   1  one step of all workspaces (one graph branch each) captured into a
- *      hipGraph on first use (again when dt, P_device or a launch shape
- *      change) and replayed n_steps times;
+ *   1  a batch of one workspace: its step captured into a hipGraph on first
+ *      use (again when dt, P_device or a launch shape change) and replayed
+ *      n_steps times; of several: as 0;
  *   2  as 1, for batches of one dtype, L <= 32, no split layout,
  *      reorthogonalisation 0 or 1, vectors below 4 GB and 256-thread
  *      row-streaming blocks (the default shape; a batch of B items needs B a
  *      power of two), else QK_EUNSUPPORTED before anything is enqueued.
- * All three run the same kernels on the same grids and give the same bits.
+ * All three run the same kernels on the same grids and give the same bits.  A
+ * workspace whose step takes one launch by itself may take several beside others
+ * that fill the device, with sums in another order.
  * Asynchronous.
  */
 qk_status qk_batch_run(qk_batch* b, double dt, int32_t n_steps, int32_t use_graph, double* P_device, void* stream);

@@ -373,7 +373,7 @@ def qk_batch_items(b: Batch) -> int:
 
 
 def _graph_mode(use_graph) -> int:
-    """0 (direct launches), 1 (graph of one branch per workspace) or 2 (as 1, for
+    """0 (direct launches), 1 (a graph for one workspace) or 2 (as 1, for
     the batches that qk.h lists); a bool means 0 or 1."""
     if isinstance(use_graph, bool):
         return int(use_graph)
@@ -386,7 +386,7 @@ def _graph_mode(use_graph) -> int:
 def qk_batch_run(b: Batch, dt: float, n_steps: int, use_graph: bool | int = True, out: torch.Tensor | None = None,
                  stream=None) -> torch.Tensor:
     """n_steps steps of every workspace; returns the device tensor P[n_steps, items].
-    use_graph: 0/False direct launches, 1/True one graph branch per workspace,
+    use_graph: 0/False direct launches, 1/True a graph if there is one workspace,
     2 as 1 for batches of one dtype (QkError for the others, see qk.h)."""
     items = qk_batch_items(b)
     if out is None:

@@ -18,6 +18,7 @@
 // records |<psi0, psi>|^2).  Every step also advances the temporal
 // autocorrelation C(t) = (1/t) integral_0^t P(t') dt' of Sec. 4 by the
 // trapezoid rule on the step grid, from the creation of the batch on.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -405,12 +406,42 @@ void batch_destroy(qk_batch* b) {
 
 // One step of every workspace, each on its own stream forked from `s` and
 // joined back, then the autocorrelation advances and the step counter moves on.
+// Which workspaces of a batch take the passes although the step in one launch
+// covers them: all, where the others have more than kBesideElements elements
+// (their kernels fill the compute units that its work-groups would wait for: 64
+// phases of the 20-site ring with single rings of 16, 18, 20 and 22 sites 15.2
+// against 14.7 ms); else those whose work-groups, the fewest first, take more
+// than half the compute units, and may find no place together (18 sites, 4
+// phases, with 17 sites: 4.4 against 2.3 ms; below that, 15 sites, 8 phases,
+// with 14, 10 and 12 sites: 0.56 against 1.87 ms).
+constexpr uint64_t kBesideElements = 4000000;
+static std::vector<bool> batch_beside(const qk_batch* b) {
+  const size_t n = b->ks.size();
+  std::vector<bool> out(n, false);
+  if (n == 1) return out;
+  uint64_t others = 0;
+  std::vector<std::pair<int, size_t>> covered;
+  for (size_t i = 0; i < n; ++i) {
+    const int g = resident_groups(b->ks[i]);
+    if (g > 0) covered.push_back({g, i});
+    else others += (uint64_t)b->ks[i]->D * b->ks[i]->batch;
+  }
+  std::sort(covered.begin(), covered.end());
+  int groups = 0;
+  for (const auto& c : covered) {
+    out[c.second] = others > kBesideElements || groups + c.first > qk_num_cus() / 2;
+    if (!out[c.second]) groups += c.first;
+  }
+  return out;
+}
+
 static qk_status batch_step(qk_batch* b, double dt, double* P, double* C, hipStream_t s) {
+  const std::vector<bool> beside = batch_beside(b);
   QK_HIP(hipEventRecord(b->fork, s));
   for (size_t i = 0; i < b->ks.size(); ++i) {
     hipStream_t si = b->streams[i];
     QK_HIP(hipStreamWaitEvent(si, b->fork, 0));
-    qk_status st = launch_krylov_step(b->ks[i], b->psi[i], dt, si, StepUpTo::combination, b->ks.size() > 1);
+    qk_status st = launch_krylov_step(b->ks[i], b->psi[i], dt, si, StepUpTo::combination, beside[i]);
     if (st != QK_OK) return st;
     st = record_item(b, (int)i, P, si);
     if (st != QK_OK) return st;
@@ -481,7 +512,10 @@ qk_status batch_run(qk_batch* b, double dt, int n_steps, int use_graph, double* 
     return hip_fail(le, "qk_batch_run counter reset");
   }
   qk_status st = QK_OK;
-  if (!use_graph) {
+  // Several workspaces are launched directly on their streams: a run of 500
+  // replays of a graph with five branches has ended in a segmentation fault of
+  // the host inside the runtime, of unknown cause.
+  if (!use_graph || b->ks.size() > 1) {
     for (int k = 0; k < n_steps && st == QK_OK; ++k) st = batch_step(b, dt, P, C, s);
     restore();
     return st;

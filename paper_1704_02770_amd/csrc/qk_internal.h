@@ -227,9 +227,10 @@ struct AdaptiveStep {
 // adaptive step of at most tau.  Where *done is false, the exponential and the
 // combination are left to the passes' kernels (|u_m|^2 in d_partB).
 bool resident_covers(const qk_krylov* k);
+int resident_groups(const qk_krylov* k);   // its work-groups, 0 where it does not cover the workspace
 qk_status launch_resident(qk_krylov* k, void* psi, double rtol, double tau, StepUpTo upto, const AdaptiveStep* ad,
                           hipStream_t s, bool* done);
-// beside: steps of other workspaces run on other streams at the same time.
+// beside: by the passes, as steps of other workspaces fill the chip meanwhile.
 qk_status launch_krylov_step(qk_krylov* k, void* psi, double dt, hipStream_t s,
                              StepUpTo upto = StepUpTo::combination, bool beside = false);
 // One step of at most tau_max whose length the device chooses from the error

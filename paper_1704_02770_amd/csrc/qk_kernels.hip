@@ -603,11 +603,8 @@ static qk_status krylov_step_t(qk_krylov* k, void* psi_v, double dt, hipStream_t
     pB = spB[m & 1];
     GB = Glo;
   }
-  // small sectors: one launch for the whole step; kernel by kernel while
-  // they are being timed, and beside other workspaces' steps, whose kernels
-  // fill the compute units that its work-groups would wait for (64 phases of
-  // the 20-site ring with single rings of 16, 18 and 22 sites: 15.2 ms with
-  // it, 14.7 ms without)
+  // small sectors: one launch for the whole step; kernel by kernel while they
+  // are being timed, and beside other workspaces that fill the chip
   const bool resident = resident_covers(k) && !k->profiling && !beside;
   if (resident) {
     bool done = false;

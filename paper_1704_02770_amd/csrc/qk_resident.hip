@@ -1063,6 +1063,12 @@ bool resident_covers(const qk_krylov* k) {
   return k->d_res && (olo == 0 || olo == 9 || olo == 10);
 }
 
+int resident_groups(const qk_krylov* k) {
+  if (!resident_covers(k)) return 0;
+  const uint64_t lanes = resident_lanes(k);
+  return resident_shape(lanes, lanes / (uint64_t)k->D).groups;
+}
+
 qk_status launch_resident(qk_krylov* k, void* psi, double rtol, double tau, StepUpTo upto, const AdaptiveStep* ad,
                           hipStream_t s, bool* done) {
   const qk_ham* H = k->H;

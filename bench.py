@@ -16,7 +16,7 @@ complex128 chain from the Neel state to t = 100 with error-controlled steps
 (tolerance 1e-7 per unit time), the evolution the paper times in Sec. 5, and
 reports its step count and wall time; `mixed` times the batched workload of
 64 phases of the L = 20 ring plus single rings of L = 16, 18, 20, 22 (h = 2,
-complex64, one hipGraph replay per step, and in the default launch shape the
+complex64, a stream per member, and in the default launch shape the
 use_graph = 1 against use_graph = 2, which runs the same launches); `large` times Krylov steps of the
 L = 30 ring (m = 20, dt = 0.05, complex128 and complex64).  Every rate is the
 median of --repeats timed runs of exactly --steps steps.  Also reported: standalone
@@ -151,7 +151,7 @@ def run_form(qk, torch, b, fields, m, dt, dtype, steps, warmup, r0, repeats, pbc
 def run_mixed(qk, torch, steps, warmup, repeats, m=30, dt=0.1, h=2.0, tune=True):
     """The batched workload: 64 phases of the L = 20 ring and single rings of
     L = 16, 18, 20, 22 (h = 2, Neel state, complex64 vectors, FP64 Lanczos
-    coefficients), one hipGraph replay per step for all of them; also the
+    coefficients), every workspace on a stream of its own; also the
     64-phase workspace's kernels timed alone with HIP events (eager steps)."""
     from workloads import BETA_GOLDEN, phases
     spec = [(20, 64, 0), (16, 1, 1), (18, 1, 2), (20, 1, 3), (22, 1, 4)]
@@ -184,7 +184,7 @@ def run_mixed(qk, torch, steps, warmup, repeats, m=30, dt=0.1, h=2.0, tune=True)
         torch.cuda.synchronize()
         secs.append(time.perf_counter() - t0)
     sec = statistics.median(secs)
-    # the same members in the default launch shape, one hipGraph of plain
+    # the same members in the default launch shape, use_graph = 1 and 2:
     # launches per step against use_graph = 2 (which takes 256-thread
     # row-streaming blocks)
     for k in ks:
@@ -624,9 +624,9 @@ def main():
             traffic = tr.get("bytes_per_launch")
     roof = hpass_roofline(head["prof"], m, D, B_head, 16 if head_form == "fp64" else 8, traffic)
     roof["kernel"] = ("H-pass of the Lanczos iteration, w = a H u_j - b u_{j-1} with its dot products "
-                      + {"fp64": "(k_blk<double,11,true>, the blocked matrix-free kernel used for L >= 18)",
-                         "fp32": "(k_blk<float,11,true>, complex64 storage)",
-                         "batched": f"(k_blkb<float,true>, {args.batch} phases in complex64)"}[head_form])
+                      + {"fp64": "(k_tile<double,...>, the tiled matrix-free kernel of chains of 8 to 32 sites)",
+                         "fp32": "(k_tile<float,...>, complex64 storage)",
+                         "batched": f"(k_tile<float,...>, {args.batch} phases in complex64)"}[head_form])
     roof["form"] = head_form
 
     def form_summary(r, B, s, m_, D_, steps_):
@@ -673,7 +673,7 @@ def main():
         out["mixed"] = dict(
             workload="64 phases of the L=20 ring (D=184756) + rings L=16,18,20,22 (one phase each), h=2, "
                      "J=Delta=1, Neel state, m=30, dt=0.1, complex64 vectors, FP64 Lanczos coefficients; "
-                     "all members advanced by one hipGraph replay per step",
+                     "every member on a stream of its own",
             items=mixed["items"], steps=mixed["steps"], phase_steps_per_s=round(mixed["phase_steps_per_s"], 1),
             steps_per_s=round(mixed["steps_per_s"], 2), ms_per_step=round(1e3 * mixed["sec"] / mixed["steps"], 3),
             ms_per_step_runs=[round(1e3 * x / mixed["steps"], 3) for x in mixed["sec_all"]],
@@ -681,7 +681,7 @@ def main():
                 graph_ms_per_step=round(1e3 * mixed["sec_graph_default"] / mixed["steps"], 3),
                 graph2_ms_per_step=round(1e3 * mixed["sec_graph2"] / mixed["steps"], 3),
                 graph2_phase_steps_per_s=round(mixed["items"] * mixed["steps"] / mixed["sec_graph2"], 1),
-                note="the members in the default launch shape: one hipGraph of plain launches per step, and "
+                note="the members in the default launch shape: use_graph=1, and "
                      "use_graph=2, which runs the same launches"),
             roofline_L20x64=hpass_roofline(mixed["prof64"], 30, mixed["D20"], 64, 8, None),
             kernels_L20x64={kname: dict(ms_per_launch=ms_ / max(n_, 1), launches=n_)

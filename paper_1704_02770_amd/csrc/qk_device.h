@@ -394,6 +394,73 @@ __device__ __forceinline__ void tri_expm_e1(double al, double be, double bl, boo
   ei = vr * ci + vi * cr;
 }
 
+// Largest v >= 0 of the wave, in every lane.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_max(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROWS, 0xf, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROWS, 0xf, false);
+  return fmax(v, __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo));
+}
+__device__ __forceinline__ double wave_max(double v) {
+  v = dpp_max<0x111, 0xf>(v);   // from the lane 1, 2, 4, 8 below in a row of 16
+  v = dpp_max<0x112, 0xf>(v);
+  v = dpp_max<0x114, 0xf>(v);
+  v = dpp_max<0x118, 0xf>(v);
+  v = dpp_max<0x142, 0xa>(v);   // the last lane of row 0 (2) to row 1 (3)
+  v = dpp_max<0x143, 0xc>(v);   // the last lane of the first half to the second
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, 63);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 63);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// The same by a Taylor series in substeps of |tau| R <= 1/2 that end where the
+// terms fall below 1e-18 of the sum.  Components smaller than that come out
+// smaller than they are, or zero; the step-size rule, whose estimate is such a
+// component after a short step, keeps the steps that follow from it.  Neighbours
+// and maxima go through the data-parallel moves of the vector unit (by shuffles
+// a call took 100 us).
+__device__ __forceinline__ void tri_expm_e1_taylor(double al, double be, double bl, bool on, int i, double tau, double& er,
+                                                   double& ei) {
+  double lo = on ? al - be - bl : INFINITY, hi = on ? al + be + bl : -INFINITY;
+  for (int s = 32; s > 0; s >>= 1) {
+    lo = fmin(lo, __shfl_xor(lo, s));
+    hi = fmax(hi, __shfl_xor(hi, s));
+  }
+  const double mu_shift = 0.5 * (lo + hi);
+  const double radius = 0.5 * (hi - lo);
+  const double ad = on ? al - mu_shift : 0.0;
+  // bounded substep count (a non-finite or huge norm cannot stall the wave)
+  const double nsd = ceil(fabs(tau) * radius / 0.5);
+  const int nsub = (nsd >= 1.0 && nsd <= 100000.0) ? (int)nsd : (nsd > 100000.0 ? 100000 : 1);
+  const double ts = tau / nsub;
+  double vr = (i == 0) ? 1.0 : 0.0, vi = 0.0;
+  for (int sub = 0; sub < nsub; ++sub) {
+    double sr = vr, si = vi, tr = vr, ti = vi;
+    for (int k = 1; k <= 40; ++k) {
+      // t <- (-i ts / k) (T - mu) t
+      const double up_r = wave_next<true>(tr), up_i = wave_next<true>(ti);
+      const double dn_r = wave_next<false>(tr), dn_i = wave_next<false>(ti);
+      double yr = ad * tr + (i > 0 ? bl * up_r : 0.0) + (i < 63 ? be * dn_r : 0.0);
+      double yi = ad * ti + (i > 0 ? bl * up_i : 0.0) + (i < 63 ? be * dn_i : 0.0);
+      if (!on) yr = yi = 0.0;
+      const double f = ts / k;
+      tr = f * yi;    // (-i f) (yr + i yi) = f yi - i f yr
+      ti = -f * yr;
+      sr += tr;
+      si += ti;
+      const double tn = wave_max(fabs(tr) + fabs(ti)), sn = wave_max(fabs(sr) + fabs(si));
+      if (tn <= 1e-18 * sn) break;
+    }
+    vr = sr;
+    vi = si;
+  }
+  const double cr = cos(tau * mu_shift), ci = -sin(tau * mu_shift);
+  er = vr * cr - vi * ci;
+  ei = vr * ci + vi * cr;
+}
+
 // Scalars of the H-pass of Lanczos iteration j for every batch column b,
 // from the update pass of iteration j-1 (its partial sums |u_j|^2):
 //   sa[b] = sigma_j, sb[b] = beta_{j-1} sigma_{j-1}, act[b] = column still running.

@@ -58,7 +58,8 @@ typedef enum {
   QK_ENOMEM = 2,        /* device allocation failed */
   QK_EHIP = 3,          /* a HIP runtime call failed (text in qk_last_error) */
   QK_EUNSUPPORTED = 4,  /* valid request outside what the library implements */
-  QK_ENUMERIC = 5       /* non-finite Lanczos coefficient, or an adaptive evolution that could not reach t */
+  QK_ENUMERIC = 5       /* non-finite Lanczos coefficient, an adaptive evolution that could not reach t, or a
+                           wait inside a step that gave up (see qk_krylov_create; text in qk_last_error) */
 } qk_status;
 
 typedef enum { QK_C128 = 0, QK_C64 = 1 } qk_dtype;
@@ -222,6 +223,17 @@ typedef struct qk_krylov qk_krylov;
  * all previous vectors, dot products and coefficients in double; about
  * 4 (j + 2) extra vector reads at iteration j).  The Hamiltonian must outlive
  * the workspace.
+ *
+ * Matrix-free sectors of L <= 20 with up to 8 columns (rounded up to a power
+ * of two) and 196,608 elements in all, reorth 0 or 1, take a step in one
+ * launch, whose work-groups wait for one another.  A wait that has polled
+ * 2^24 times without success (about 10 s of running) gives up: the step then
+ * leaves psi as it was, and so does every later one of the workspace.  They
+ * report QK_ENUMERIC (qk_krylov_expm_step with info, qk_krylov_evolve,
+ * qk_grad_return_prob) or record NaN (qk_batch_run).  For tests, two
+ * environment variables are read at this call: QK_RESIDENT_POLLS=n gives up
+ * after n polls (0: at once), QK_RESIDENT_JOIN=n lets n work-groups take all
+ * rows.
  */
 qk_status qk_krylov_create(const qk_ham* H, int32_t m, int32_t dtype, int32_t reorth, qk_krylov** out);
 

@@ -83,6 +83,12 @@ static bool ranges_overlap(const void* a, size_t na, const void* b, size_t nb) {
 
 int krylov_grid(uint64_t D, int B);
 
+// Why a step of k failed on the device.
+static const char* numeric_reason(const qk_krylov* k) {
+  return resident_gave_up(k) ? "a wait between the work-groups of a step gave up; the workspace is no longer usable"
+                             : "non-finite Lanczos coefficient";
+}
+
 // psi (n bytes) intersects the workspace's own vectors (the basis slots, z)
 static bool workspace_overlap(const qk_krylov* k, const void* psi, size_t n) {
   const size_t slot = elem_bytes(k->dtype) * (size_t)k->ustride;
@@ -419,6 +425,8 @@ qk_status qk::krylov_create(const qk_ham* H, int32_t m, int32_t dtype, int32_t r
     k->d_X = (char*)k->d_res + ctl;
     // QK_RESIDENT_JOIN=n, read here: only n work-groups register
     if (const char* ev = getenv("QK_RESIDENT_JOIN")) k->res_join = std::max(0, atoi(ev));
+    // QK_RESIDENT_POLLS=n: a wait between work-groups gives up after n polls
+    if (const char* ev = getenv("QK_RESIDENT_POLLS")) k->res_polls = (uint32_t)std::max(0, atoi(ev));
   }
   if (e == hipSuccess && reorth == 2) {
     const size_t chunks = (size_t)(m + kReorthChunk - 1) / kReorthChunk;
@@ -466,7 +474,7 @@ QK_API qk_status qk_krylov_expm_step(qk_krylov* k, void* psi, double dt, void* s
     info[b].beta0 = n0[b];
     if (iv[B + b] != QK_OK) worst = QK_ENUMERIC;
   }
-  if (worst != QK_OK) set_error("non-finite Lanczos coefficient");
+  if (worst != QK_OK) set_error(numeric_reason(k));
   return worst;
 }
 
@@ -505,7 +513,7 @@ QK_API qk_status qk_krylov_evolve(qk_krylov* k, void* psi, double t, const qk_ad
     const double e0 = err[0];
     for (int b = 0; b < B; ++b)
       if (std::isnan(tau[B + b])) {
-        set_error("non-finite Lanczos coefficient");
+        set_error(numeric_reason(k));
         return QK_ENUMERIC;
       }
     double acc = tau[0], nxt = tau[B];

@@ -36,8 +36,8 @@ namespace qk {
 // ----------------------------------------------------------------- kernels
 template <typename T>
 __global__ void k_record(const typename Cx<T>::V* __restrict__ psi, uint32_t r0, int B, double* __restrict__ P,
-                         const int* __restrict__ counter, int off, int items) {
-  record_body<T>(psi, r0, B, P, counter, off, items);
+                         const int* __restrict__ counter, int off, int items, const uint32_t* __restrict__ gave_up) {
+  record_body<T>(psi, r0, B, P, counter, off, items, gave_up);
 }
 
 __global__ void k_counter(int* counter, int reset) {
@@ -71,10 +71,10 @@ static qk_status launch_record(const qk_krylov* k, const void* psi, int64_t r0, 
                                int items, hipStream_t s) {
   if (k->dtype == QK_C128)
     hipLaunchKernelGGL(k_record<double>, dim3(1), dim3(64), 0, s, (const double2*)psi, (uint32_t)r0, k->batch, P,
-                       counter, off, items);
+                       counter, off, items, resident_verdict(k));
   else
     hipLaunchKernelGGL(k_record<float>, dim3(1), dim3(64), 0, s, (const float2*)psi, (uint32_t)r0, k->batch, P,
-                       counter, off, items);
+                       counter, off, items, resident_verdict(k));
   QK_HIP(hipGetLastError());
   return QK_OK;
 }
@@ -313,7 +313,7 @@ static qk_status record_item(qk_batch* b, int i, double* P, hipStream_t s) {
   if (b->r0[i] >= 0)
     return launch_record(k, b->psi[i], b->r0[i], P, b->d_counter, b->item_off[i], b->items, s);
   return launch_overlap_record(b->psi0[i], b->psi[i], k->dtype, (uint32_t)k->D, k->batch, b->part[i], b->ogrid[i], P,
-                               b->d_counter, b->item_off[i], b->items, s);
+                               b->d_counter, b->item_off[i], b->items, resident_verdict(k), s);
 }
 int batch_device(const qk_batch* b) { return b->device; }
 

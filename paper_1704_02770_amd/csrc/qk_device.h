@@ -461,6 +461,11 @@ __device__ __forceinline__ void tri_expm_e1_taylor(double al, double be, double 
   ei = vr * ci + vi * cr;
 }
 
+// A workspace whose step has given up (resident_verdict): its state stays behind.
+__device__ __forceinline__ bool left_behind(const uint32_t* __restrict__ gave_up) {
+  return gave_up && *gave_up == kResGaveUp;
+}
+
 // Scalars of the H-pass of Lanczos iteration j for every batch column b,
 // from the update pass of iteration j-1 (its partial sums |u_j|^2):
 //   sa[b] = sigma_j, sb[b] = beta_{j-1} sigma_{j-1}, act[b] = column still running.

@@ -348,9 +348,12 @@ k_grad_contract(const S* __restrict__ states, uint64_t niter, int L, GradSteps g
 
 // Totals of the n rows of partial sums in a fixed order: kAccLanes lanes per
 // column each add every kAccLanes-th row, then the lanes are added pairwise.
+// tot[kGradQ]: whether a wait has given up in one of the two workspaces
+// (resident_verdict), which leaves its steps out.
 constexpr int kAccCols = 8, kAccLanes = 128;
 __global__ void __launch_bounds__(kAccCols * kAccLanes)
-k_grad_total(const double* __restrict__ part, int n, double* __restrict__ tot) {
+k_grad_total(const double* __restrict__ part, int n, const uint32_t* __restrict__ gave_up_f,
+             const uint32_t* __restrict__ gave_up_b, double* __restrict__ tot) {
   __shared__ double red[kAccLanes][kAccCols];
   const int c = threadIdx.x % kAccCols, l = threadIdx.x / kAccCols, col = blockIdx.x * kAccCols + c;
   double acc = 0.0;
@@ -362,6 +365,8 @@ k_grad_total(const double* __restrict__ part, int n, double* __restrict__ tot) {
     if (l < h) red[l][c] += red[l + h][c];
   }
   if (l == 0 && col < kGradQ) tot[col] = red[0][c];
+  if (blockIdx.x == 0 && threadIdx.x == 0)
+    tot[kGradQ] = left_behind(gave_up_f) || left_behind(gave_up_b) ? 1.0 : 0.0;
 }
 
 __global__ void k_basis_vector(double2* __restrict__ v, uint32_t D, uint32_t r0) {
@@ -461,7 +466,7 @@ qk_status grad_return_prob(qk_krylov* k, int64_t r0, double T, int n_steps, int 
                                tiles / (8 * kGcWaves)));
   const size_t pbytes = sizeof(double) * (size_t)S * G * kGradQ;
   if (e == hipSuccess) e = dev_alloc(k->al, (void**)&part, pbytes);
-  if (e == hipSuccess) e = dev_alloc(k->al, (void**)&tot, sizeof(double) * kGradQ);
+  if (e == hipSuccess) e = dev_alloc(k->al, (void**)&tot, sizeof(double) * (kGradQ + 1));
   if (e == hipSuccess) e = hipMemsetAsync(part, 0, pbytes, s);
   const GaussRule gr = gauss_legendre();
   auto chk = [&](const char* what) {
@@ -585,16 +590,20 @@ qk_status grad_return_prob(qk_krylov* k, int64_t r0, double T, int n_steps, int 
     contract(gs, (n_steps - 1 - t) % S, 1);
     std::swap(mir, mnext);
   }
-  std::vector<double> th(kGradQ);
+  std::vector<double> th(kGradQ + 1);
   if (st == QK_OK) {
     hipLaunchKernelGGL(k_grad_total, dim3((kGradQ + kAccCols - 1) / kAccCols), dim3(kAccCols * kAccLanes), 0, s,
-                       (const double*)part, S * G, tot);
+                       (const double*)part, S * G, resident_verdict(k), kb ? resident_verdict(kb) : nullptr, tot);
     chk("k_grad_total");
   }
   if (st == QK_OK) {
-    e = hipMemcpyAsync(th.data(), tot, sizeof(double) * kGradQ, hipMemcpyDeviceToHost, s);
+    e = hipMemcpyAsync(th.data(), tot, sizeof(double) * (kGradQ + 1), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) st = hip_fail(e, "qk_grad_return_prob readback");
+  }
+  if (st == QK_OK && th[kGradQ] != 0.0) {
+    set_error("a wait between the work-groups of a step gave up; the workspace is no longer usable");
+    st = QK_ENUMERIC;
   }
   if (st == QK_OK) {
     *F = A.x * A.x + A.y * A.y;

@@ -29,6 +29,8 @@ template <> struct StateT<uint64_t> {
 };
 constexpr int kNumXcd = 8;              // MI355X: 8 accelerator complex dies, WGs dealt round-robin
 constexpr int kMaxBlock = 256;
+constexpr uint32_t kResPolls = 1u << 24;   // polls of a wait between work-groups, about 10 s of running
+constexpr uint32_t kResGaveUp = 2;      // verdict of a one-launch step of which a wait has given up
 constexpr int kReorthChunk = 8;         // Krylov vectors per dot-product pass of the full reorthogonalisation
 constexpr int kReorthGrid = 512;        // blocks of that pass
 constexpr int kMaxPartialBlocks = 4096; // partial-sum slots per reduction (>= any grid used)
@@ -142,6 +144,7 @@ struct qk_krylov {
   void* d_res = nullptr;          // resident recurrence of small sectors (qk_resident.hip): control words
   void* d_X = nullptr;            // and its two exchange vectors (both in the coefficients' allocation)
   int res_join = 0;               // work-groups that may register there (0: all)
+  uint32_t res_polls = qk::kResPolls;   // polls of a wait there before it gives up
   // event timing (qk_krylov_profile)
   bool profiling = false;
   struct Pending { int kind; hipEvent_t start, end; };
@@ -227,6 +230,10 @@ struct AdaptiveStep {
 // adaptive step of at most tau.  Where *done is false, the exponential and the
 // combination are left to the passes' kernels (|u_m|^2 in d_partB).
 bool resident_covers(const qk_krylov* k);
+// Device word that equals kResGaveUp once a wait of the workspace has given up
+// (its steps fail from then on); NULL where there is none.
+const uint32_t* resident_verdict(const qk_krylov* k);
+bool resident_gave_up(const qk_krylov* k);   // waits for the device
 int resident_groups(const qk_krylov* k);   // its work-groups, 0 where it does not cover the workspace
 qk_status launch_resident(qk_krylov* k, void* psi, double rtol, double tau, StepUpTo upto, const AdaptiveStep* ad,
                           hipStream_t s, bool* done);
@@ -240,8 +247,10 @@ qk_status launch_krylov_step(qk_krylov* k, void* psi, double dt, hipStream_t s,
 // record position (counter == NULL: P[b]); part holds G * 2 * B doubles with
 // G = overlap_grid(D, B).
 int overlap_grid(uint32_t D, int B);
+// gave_up: resident_verdict of the workspace; NaN is recorded for a state that it has left behind.
 qk_status launch_overlap_record(const void* psi0, const void* psi, int dtype, uint32_t D, int B, double* part, int G,
-                                double* P, const int* counter, int off, int items, hipStream_t s);
+                                double* P, const int* counter, int off, int items, const uint32_t* gave_up,
+                                hipStream_t s);
 qk_status launch_krylov_adaptive_step(qk_krylov* k, void* psi, double tau_max, double tol, hipStream_t s);
 qk_status grad_return_prob(qk_krylov* k, int64_t r0, double T, int n_steps, int ckpt_every, double* F, double* dFdh,
                            hipStream_t s);

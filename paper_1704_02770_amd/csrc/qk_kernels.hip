@@ -268,10 +268,10 @@ k_overlap_partial(const typename Cx<T>::V* __restrict__ psi0, const typename Cx<
 // P[(*counter) * items + off + b] (the batched driver's record layout).
 __global__ void __launch_bounds__(kMaxBlock)
 k_overlap_final(const double* __restrict__ part, int G, int B, double* P, const int* __restrict__ counter, int off,
-                int items) {
+                int items, const uint32_t* __restrict__ gave_up) {
   __shared__ double red[kMaxBlock];
   __shared__ double tot[2 * QK_MAX_BATCH];
-  overlap_final_body(red, tot, part, G, B, P, counter, off, items);
+  overlap_final_body(red, tot, part, G, B, P, counter, off, items, gave_up);
 }
 
 
@@ -772,7 +772,8 @@ qk_status launch_return_prob(const qk_basis* b, int64_t r0, const void* psi0, co
                        (const float2*)psi, D, B, part);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_overlap_final, dim3(1), dim3(kMaxBlock), 0, s, part, G, B, P, (const int*)nullptr, 0, 0);
+    hipLaunchKernelGGL(k_overlap_final, dim3(1), dim3(kMaxBlock), 0, s, part, G, B, P, (const int*)nullptr, 0, 0,
+                       (const uint32_t*)nullptr);
     e = hipGetLastError();
   }
   QK_HIP(dev_free_async(b->al, part, s));
@@ -833,7 +834,8 @@ qk_status launch_return_prob_noalloc(const qk_basis* b, int64_t r0, const void* 
     hipLaunchKernelGGL(k_overlap_partial<float>, dim3(G), dim3(threads), 0, s, (const float2*)psi0,
                        (const float2*)psi, D, B, part);
   QK_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_overlap_final, dim3(1), dim3(kMaxBlock), 0, s, part, G, B, P, (const int*)nullptr, 0, 0);
+  hipLaunchKernelGGL(k_overlap_final, dim3(1), dim3(kMaxBlock), 0, s, part, G, B, P, (const int*)nullptr, 0, 0,
+                       (const uint32_t*)nullptr);
   QK_HIP(hipGetLastError());
   return QK_OK;
 }
@@ -841,7 +843,8 @@ qk_status launch_return_prob_noalloc(const qk_basis* b, int64_t r0, const void* 
 int overlap_grid(uint32_t D, int B) { return stream_grid(D, B, block_threads(B), 0); }
 
 qk_status launch_overlap_record(const void* psi0, const void* psi, int dtype, uint32_t D, int B, double* part, int G,
-                                double* P, const int* counter, int off, int items, hipStream_t s) {
+                                double* P, const int* counter, int off, int items, const uint32_t* gave_up,
+                                hipStream_t s) {
   const int threads = block_threads(B);
   if (dtype == QK_C128)
     hipLaunchKernelGGL(k_overlap_partial<double>, dim3(G), dim3(threads), 0, s, (const double2*)psi0,
@@ -850,7 +853,8 @@ qk_status launch_overlap_record(const void* psi0, const void* psi, int dtype, ui
     hipLaunchKernelGGL(k_overlap_partial<float>, dim3(G), dim3(threads), 0, s, (const float2*)psi0,
                        (const float2*)psi, D, B, part);
   QK_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_overlap_final, dim3(1), dim3(kMaxBlock), 0, s, part, G, B, P, counter, off, items);
+  hipLaunchKernelGGL(k_overlap_final, dim3(1), dim3(kMaxBlock), 0, s, part, G, B, P, counter, off, items,
+                     gave_up);
   QK_HIP(hipGetLastError());
   return QK_OK;
 }

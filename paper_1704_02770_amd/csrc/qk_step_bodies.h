@@ -467,10 +467,12 @@ __device__ __forceinline__ void overlap_partial_body(VRange rg, double* red, con
 // red: LDS of blockDim doubles, tot: of 2 * QK_MAX_BATCH doubles; one block.
 __device__ __forceinline__ void overlap_final_body(double* red, double* tot, const double* __restrict__ part, int G,
                                                    int B, double* P, const int* __restrict__ counter, int off,
-                                                   int items) {
+                                                   int items, const uint32_t* __restrict__ gave_up) {
   reduce_partials(part, G, 2, B, red, tot);
   double* out = counter ? P + (size_t)(*counter) * items + off : P;
-  for (int b = threadIdx.x; b < B; b += blockDim.x) out[b] = tot[b] * tot[b] + tot[B + b] * tot[B + b];
+  const bool lost = left_behind(gave_up);
+  for (int b = threadIdx.x; b < B; b += blockDim.x)
+    out[b] = lost ? NAN : tot[b] * tot[b] + tot[B + b] * tot[B + b];
 }
 
 // ------------------------------------------------ batched driver records
@@ -479,11 +481,12 @@ __device__ __forceinline__ void overlap_final_body(double* red, double* tot, con
 template <typename T>
 __device__ __forceinline__ void record_body(const typename Cx<T>::V* __restrict__ psi, uint32_t r0, int B,
                                             double* __restrict__ P, const int* __restrict__ counter, int off,
-                                            int items) {
+                                            int items, const uint32_t* __restrict__ gave_up) {
   const int b = threadIdx.x;
   if (b >= B) return;
   const typename Cx<T>::V v = psi[(size_t)r0 * B + b];
-  P[(size_t)(*counter) * items + off + b] = (double)v.x * (double)v.x + (double)v.y * (double)v.y;
+  P[(size_t)(*counter) * items + off + b] =
+      left_behind(gave_up) ? NAN : (double)v.x * (double)v.x + (double)v.y * (double)v.y;
 }
 
 // Trapezoid step of the autocorrelation integral for every item: S += dt/2

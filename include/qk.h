@@ -226,7 +226,10 @@ typedef struct qk_krylov qk_krylov;
  *
  * Matrix-free sectors of L <= 20 with up to 8 columns (rounded up to a power
  * of two) and 196,608 elements in all, reorth 0 or 1, take a step in one
- * launch, whose work-groups wait for one another.  A wait that has polled
+ * launch, whose work-groups wait for one another.  Such steps of several
+ * workspaces on different streams run side by side where all their work-groups
+ * find a place on the device, else in the order of the calls (a step then
+ * waits on the device for earlier ones on other streams).  A wait that has polled
  * 2^24 times without success (about 10 s of running) gives up: the step then
  * leaves psi as it was, and so does every later one of the workspace.  They
  * report QK_ENUMERIC (qk_krylov_expm_step with info, qk_krylov_evolve,

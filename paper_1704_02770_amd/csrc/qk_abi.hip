@@ -442,6 +442,7 @@ qk_status qk::krylov_create(const qk_ham* H, int32_t m, int32_t dtype, int32_t r
     qk_krylov_destroy(k);
     return st;
   }
+  resident_register(k);
   *out = k;
   return QK_OK;
 }
@@ -600,6 +601,7 @@ QK_API qk_status qk_krylov_profile_read(qk_krylov* k, qk_kernel_time* out) {
 QK_API void qk_krylov_destroy(qk_krylov* k) {
   if (!k) return;
   (void)hipDeviceSynchronize();
+  resident_unregister(k);
   for (auto& p : k->pending) {
     if (p.start) (void)hipEventDestroy(p.start);
     if (p.end) (void)hipEventDestroy(p.end);

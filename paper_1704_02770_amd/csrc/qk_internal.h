@@ -145,6 +145,12 @@ struct qk_krylov {
   void* d_X = nullptr;            // and its two exchange vectors (both in the coefficients' allocation)
   int res_join = 0;               // work-groups that may register there (0: all)
   uint32_t res_polls = qk::kResPolls;   // polls of a wait there before it gives up
+  // order of such steps on several streams (resident_order); under its mutex
+  qk_krylov *res_prev = nullptr, *res_next = nullptr;
+  hipEvent_t res_event = nullptr;   // after its last launch that was ordered
+  hipStream_t res_stream = nullptr; // of its last launch
+  bool res_launched = false;
+  int res_share = 0;                // compute units that its work-groups fill, 0: not known yet
   // event timing (qk_krylov_profile)
   bool profiling = false;
   struct Pending { int kind; hipEvent_t start, end; };
@@ -230,6 +236,10 @@ struct AdaptiveStep {
 // adaptive step of at most tau.  Where *done is false, the exponential and the
 // combination are left to the passes' kernels (|u_m|^2 in d_partB).
 bool resident_covers(const qk_krylov* k);
+// Workspaces whose one-launch steps take several work-groups, between their
+// creation and their end.
+void resident_register(qk_krylov* k);
+void resident_unregister(qk_krylov* k);
 // Device word that equals kResGaveUp once a wait of the workspace has given up
 // (its steps fail from then on); NULL where there is none.
 const uint32_t* resident_verdict(const qk_krylov* k);

@@ -53,6 +53,7 @@
 // L = 12 (open, 20 vectors) 51 against 244 us, L = 16 171 against 420, L = 18
 // 217, L = 20 325 against 690; of four phases at L = 12 in complex64 182.
 #include <algorithm>
+#include <mutex>
 #include <type_traits>
 
 #include "qk_step_bodies.h"
@@ -1083,6 +1084,7 @@ struct ResLaunch {
   void *psi, *U, *X;
   KState st;
   hipStream_t s;
+  int* occupancy = nullptr;   // not NULL: receives the work-groups that a compute unit holds, instead of a launch
   template <typename T, int KMAX, int OLO>
   void one() const {
     using V = typename Cx<T>::V;
@@ -1091,6 +1093,12 @@ struct ResLaunch {
   template <typename T, int KMAX, int OLO, int NT, int LOADS>
   void many() const {
     using V = typename Cx<T>::V;
+    if (occupancy) {
+      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(occupancy, k_resident<T, KMAX, OLO, NT, LOADS, LOADS == 0>,
+                                                       sp.threads, 0) != hipSuccess)
+        *occupancy = 1;
+      return;
+    }
     hipLaunchKernelGGL((k_resident<T, KMAX, OLO, NT, LOADS, LOADS == 0>), dim3(sp.groups), dim3(sp.threads), 0, s, ra,
                        (V*)psi, (V*)U, (V*)X, st);
   }
@@ -1139,6 +1147,79 @@ int resident_groups(const qk_krylov* k) {
   return resident_shape(lanes, lanes / (uint64_t)k->D).groups;
 }
 
+// Steps on several streams.  Two launches that find no place together on the
+// compute units and come at the same time get a part of their work-groups in
+// each: both wait for the rest (kJoinTicks), then run dealt out.  Three streams
+// with the 19-site ring took 4.5 ms for a step each that way, four with 20 sites
+// 6 to 7 ms; one after another they take 0.79 and 1.33 ms (by the passes of an
+// earlier version, side by side, 1.03 and 1.19 ms).  So a launch waits, on the
+// device, for those on other streams that it does not fit beside, the latest
+// ones first in the places: of the others a second chipful is waited for,
+// which has itself waited for what came before.  Workspaces that all fit, or
+// are used on one stream, pay nothing.  A captured launch is not ordered (its
+// replays come when they come), nor are other processes.
+static std::mutex g_order_mu;
+static qk_krylov* g_order_head = nullptr;   // latest launch first
+
+static void order_unlink(qk_krylov* k) {
+  if (k->res_prev) k->res_prev->res_next = k->res_next;
+  else if (g_order_head == k) g_order_head = k->res_next;
+  if (k->res_next) k->res_next->res_prev = k->res_prev;
+  k->res_prev = k->res_next = nullptr;
+}
+
+static void order_front(qk_krylov* k) {
+  k->res_next = g_order_head;
+  if (g_order_head) g_order_head->res_prev = k;
+  g_order_head = k;
+}
+
+void resident_register(qk_krylov* k) {
+  if (!k->d_res || resident_groups(k) <= 1) return;
+  std::lock_guard<std::mutex> lk(g_order_mu);
+  order_front(k);
+}
+
+void resident_unregister(qk_krylov* k) {
+  std::lock_guard<std::mutex> lk(g_order_mu);
+  order_unlink(k);
+  if (k->res_event) (void)hipEventDestroy(k->res_event);
+  k->res_event = nullptr;
+}
+
+// Under the mutex, before a launch on s: the waits; returns whether an event is
+// to be recorded after it.
+static bool resident_order(qk_krylov* k, hipStream_t s) {
+  const int cus = qk_num_cus();
+  auto beside = [&](const qk_krylov* o) {   // may run while this launch does
+    return o != k && o->res_launched && o->device == k->device && o->res_stream != s;
+  };
+  int all = k->res_share;
+  for (const qk_krylov* o = g_order_head; o; o = o->res_next)
+    if (beside(o)) all += o->res_share;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  const bool several = all > cus;
+  if (several && (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)) {
+    (void)hipGetLastError();
+    return false;
+  }
+  int with = k->res_share, after = 0;
+  for (const qk_krylov* o = several ? g_order_head : nullptr; o && after <= cus; o = o->res_next) {
+    if (!beside(o)) continue;
+    if (with + o->res_share <= cus) {
+      with += o->res_share;
+    } else {
+      after += o->res_share;
+      if (o->res_event && hipStreamWaitEvent(s, o->res_event, 0) != hipSuccess) (void)hipGetLastError();
+    }
+  }
+  k->res_stream = s;
+  k->res_launched = true;
+  order_unlink(k);
+  order_front(k);
+  return several;
+}
+
 qk_status launch_resident(qk_krylov* k, void* psi, double rtol, double tau, StepUpTo upto, const AdaptiveStep* ad,
                           hipStream_t s, bool* done) {
   const qk_ham* H = k->H;
@@ -1181,11 +1262,32 @@ qk_status launch_resident(qk_krylov* k, void* psi, double rtol, double tau, Step
   rl.st = make_kstate(k);
   rl.s = s;
   const int olo = resident_olo(k);
-  if (k->dtype == QK_C128) rl.go<double, 0>();
-  else if (olo == 0) rl.go<float, 0>();
-  else if (olo == 9) rl.go<float, 9>();
-  else rl.go<float, 10>();
+  auto go = [&] {
+    if (k->dtype == QK_C128) rl.go<double, 0>();
+    else if (olo == 0) rl.go<float, 0>();
+    else if (olo == 9) rl.go<float, 9>();
+    else rl.go<float, 10>();
+  };
+  if (ra.groups == 1) {
+    go();
+    QK_HIP(hipGetLastError());
+    return QK_OK;
+  }
+  std::lock_guard<std::mutex> lk(g_order_mu);
+  if (k->res_share == 0) {
+    int occ = 1;
+    rl.occupancy = &occ;
+    go();
+    rl.occupancy = nullptr;
+    k->res_share = (ra.groups + std::max(1, occ) - 1) / std::max(1, occ);
+  }
+  const bool record = resident_order(k, s);
+  go();
   QK_HIP(hipGetLastError());
+  if (record) {
+    if (!k->res_event) QK_HIP(hipEventCreateWithFlags(&k->res_event, hipEventDisableTiming));
+    QK_HIP(hipEventRecord(k->res_event, s));
+  }
   return QK_OK;
 }
 

@@ -353,6 +353,8 @@ qk_status qk_krylov_get_shape(const qk_krylov* k, qk_launch_shape* shape);
  * row-streaming shape.  With a non-NULL cache_path
  * the result is looked up first and stored afterwards in that JSON file,
  * keyed by (L, n_up, boundary, batch, mode, dtype, m, reorth, compute units).
+ * A workspace whose steps take one launch (qk_krylov_create) has nothing to
+ * choose: it keeps its shape, which is timed and stored.
  * Synchronous.  *chosen (may be NULL) receives the shape.
  */
 qk_status qk_krylov_autotune(qk_krylov* k, double dt, const char* cache_path, void* stream, qk_launch_shape* chosen);

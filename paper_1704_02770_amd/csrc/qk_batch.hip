@@ -195,7 +195,11 @@ static qk_status time_step(qk_krylov* k, void* v, uint64_t n, double dt, hipStre
 
 qk_status krylov_autotune(qk_krylov* k, double dt, const char* cache_path, hipStream_t s, qk_launch_shape* chosen) {
   const std::string key = shape_key(k);
-  if (cache_path && *cache_path) {
+  // no launch shape applies to a step in one launch: the present one stays, also
+  // where the cache has another (its tiles could change the order of complex64's
+  // sums, or lead to a step of many launches)
+  const bool fixed = resident_covers(k);
+  if (!fixed && cache_path && *cache_path) {
     const auto m = read_cache(cache_path);
     const auto it = m.find(key);
     qk_launch_shape sh{};
@@ -215,7 +219,7 @@ qk_status krylov_autotune(qk_krylov* k, double dt, const char* cache_path, hipSt
   const bool prof = k->profiling;
   k->profiling = false;
   qk_status st = he == hipSuccess ? QK_OK : hip_fail(he, "qk_krylov_autotune events");
-  qk_launch_shape best{}, cur{};
+  qk_launch_shape best{};
   float best_ms = 1e30f;
   auto trial = [&](const qk_launch_shape& sh) {
     if (st != QK_OK) return;
@@ -230,15 +234,17 @@ qk_status krylov_autotune(qk_krylov* k, double dt, const char* cache_path, hipSt
   const bool blocked = k->H->llo > 0;
   const int llo0 = k->H->llo;
   // coordinate search: the low-bit count of the block decomposition with the
-  // work-groups of the blocked H-pass first, then the shape of the
-  // row-streaming kernels
-  if (blocked) {
+  // work-groups of the tiled H-pass (all that fit, then fewer) first, then the
+  // shape of the row-streaming kernels
+  if (fixed) {
+    trial(qk_launch_shape{k->threads, k->blocks_per_cu, k->blocked_wgs, llo0});
+  } else if (blocked) {
     for (int llo = llo0 - 2; llo <= llo0 + 1; ++llo) {
       if (!blocked_llo_valid(k->H, llo)) continue;
-      for (int w : {2, 4, 6, 8}) {
-        cur = qk_launch_shape{0, 0, w, llo};
-        trial(cur);
-      }
+      trial(qk_launch_shape{0, 0, 0, llo});
+      const TilePlan* tp = tile_plan(k->H, k->dtype);
+      for (int w = st == QK_OK && tp ? tile_max_wgs(*tp, k->dtype) - 1 : 0; w > 0; --w)
+        trial(qk_launch_shape{0, 0, w, llo});
     }
   } else {
     trial(qk_launch_shape{0, 0, 0, 0});
@@ -246,9 +252,8 @@ qk_status krylov_autotune(qk_krylov* k, double dt, const char* cache_path, hipSt
   const int wbest = best.blocked_wgs_per_cu, lbest = best.blocked_llo;
   for (int t : {64, 128, 256})
     for (int c : {4, 8, 16}) {
-      if (t < k->batch) continue;
-      cur = qk_launch_shape{t, c, wbest, lbest};
-      trial(cur);
+      if (t < k->batch || fixed) continue;
+      trial(qk_launch_shape{t, c, wbest, lbest});
     }
   k->profiling = prof;
   if (e0) (void)hipEventDestroy(e0);

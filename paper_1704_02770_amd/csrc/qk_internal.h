@@ -204,6 +204,7 @@ qk_status tile_fields(const qk_ham* H, hipStream_t s);   // after a change of th
 const TilePlan* tile_plan(const qk_ham* H, int dtype);   // NULL: not covered
 bool tile_wide(const TilePlan* P);   // vectors that 32-bit byte offsets do not reach
 qk_status launch_tile_apply(const TilePlan& P, int dtype, const void* x, void* y, hipStream_t s);
+int tile_max_wgs(const TilePlan& P, int dtype);   // work-groups of the H-pass that a compute unit holds
 // Valid low-bit counts of the block decomposition for this Hamiltonian
 // (empty without one), and a rebuild of the tiles at another one.
 bool blocked_llo_valid(const qk_ham* H, int llo);

@@ -965,6 +965,10 @@ static qk_status launch_tile_k(const TilePlan& P, const void* x, void* y, const 
   int occ = std::min<int>(regs, (int)(kTileLds / P.lds));
   if (occ > 3) occ = 3;
   if (occ < 1) occ = 1;
+  if (wgs_req < 0) {   // tile_max_wgs
+    *grid_out = occ;
+    return QK_OK;
+  }
   const int req = wgs_req > 0 ? wgs_req : env_int("QK_BLOCKED_WGS_PER_CU", occ);
   if (req < occ) occ = req;
   int G = qk_num_cus() * occ;
@@ -1021,6 +1025,13 @@ qk_status launch_tile_lanczos_h(const TilePlan& P, int dtype, const void* uj, co
               : launch_tile_t<double, 1>(P, uj, w, ujm1, st, la, partB, Gp, partA, grid_out, wgs, s);
   return ro ? launch_tile_t<float, 2>(P, uj, w, ujm1, st, la, partB, Gp, partA, grid_out, wgs, s)
             : launch_tile_t<float, 1>(P, uj, w, ujm1, st, la, partB, Gp, partA, grid_out, wgs, s);
+}
+
+int tile_max_wgs(const TilePlan& P, int dtype) {
+  int n = 1;
+  const qk_status st = launch_tile_lanczos_h(P, dtype, nullptr, nullptr, nullptr, KState{}, LanczosArgs{}, nullptr, 0,
+                                             nullptr, &n, -1, nullptr);
+  return st == QK_OK ? n : 1;
 }
 
 }  // namespace qk

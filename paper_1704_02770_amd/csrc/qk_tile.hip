@@ -774,6 +774,9 @@ qk_status tile_fields(const qk_ham* H, hipStream_t s) {
   return QK_OK;
 }
 
+// Order of summation (TileBuild::olo) for the low-bit count llo.
+static int tile_olo(int L, int vbytes, int llo) { return vbytes == 16 ? 0 : llo > 0 ? llo : L + 1; }
+
 // Layout of one plan; *bytes receives the device memory it needs.
 static void tile_plan_layout(const qk_ham* H, int vbytes, int llo, TilePlan* P, TileBuild* tb, size_t* bytes) {
   const int L = H->basis->L, N = H->basis->N, B = H->batch;
@@ -782,7 +785,7 @@ static void tile_plan_layout(const qk_ham* H, int vbytes, int llo, TilePlan* P, 
   P->w64 = P->nel * vbytes >= 0xffffff00ull;
   a.unit = P->w64 ? (uint32_t)(B * vbytes) : 1u;
   const int fewer = llo > 0 ? blocked_llo(L, N, B, H->p.mode) - llo : 0;
-  const int olo = vbytes == 16 ? 0 : llo > 0 ? llo : L + 1;
+  const int olo = tile_olo(L, vbytes, llo);
   size_t maxel = 0;
   tile_layout(L, N, B, tile_choice(L, N, B, vbytes, fewer, olo), olo, P->w64 ? 1u : (uint32_t)(B * vbytes), a, *tb,
               &maxel);
@@ -836,11 +839,12 @@ static void plans_free(const qk_allocator& al, TilePlan* (&P)[2]) {
 // table of top patterns would be too long: batches of some GB per column.
 constexpr int kTileMinL = 8;
 
-static bool tile_covers(const qk_ham* H, int vbytes) {
+// llo: the low-bit count that the tables are for (complex64 takes no more low
+// bits than that: 31 sites with at most four particles have 21 top bits at 9).
+static bool tile_covers(const qk_ham* H, int vbytes, int llo) {
   const int L = H->basis->L;
   if (H->p.mode != QK_MATFREE || L < kTileMinL || L > 32) return false;
-  const int olo = vbytes == 16 ? 0 : H->llo > 0 ? H->llo : L + 1;
-  const TileChoice c = tile_choice(L, H->basis->N, H->batch, vbytes, 0, olo);
+  const TileChoice c = tile_choice(L, H->basis->N, H->batch, vbytes, 0, tile_olo(L, vbytes, llo));
   return L - c.l - c.M <= kTileMaxTop;
 }
 
@@ -850,7 +854,7 @@ static qk_status plans_build(qk_ham* H, int llo, TilePlan* (&P)[2], hipStream_t 
   TileBuild tb[2] = {};
   size_t bytes[2] = {0, 0};
   for (int d = 0; d < 2; ++d) {
-    if (!tile_covers(H, d ? 16 : 8)) continue;
+    if (!tile_covers(H, d ? 16 : 8, llo)) continue;
     P[d] = new (std::nothrow) TilePlan;
     if (!P[d]) {
       plans_free(H->al, P);

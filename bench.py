@@ -16,13 +16,13 @@ complex128 chain from the Neel state to t = 100 with error-controlled steps
 (tolerance 1e-7 per unit time), the evolution the paper times in Sec. 5, and
 reports its step count and wall time; `mixed` times the batched workload of
 64 phases of the L = 20 ring plus single rings of L = 16, 18, 20, 22 (h = 2,
-complex64, a stream per member, and in the default launch shape the
-use_graph = 1 against use_graph = 2, which runs the same launches); `large` times Krylov steps of the
-L = 30 ring (m = 20, dt = 0.05, complex128 and complex64).  Every rate is the
-median of --repeats timed runs of exactly --steps steps.  Also reported: standalone
-y = H x throughput (algorithmic bytes 2 s D per call), a device-copy ceiling,
-the roofline of the dominant kernel from HIP events recorded on the step's
-stream, and the CPU oracle timed on a bounded sample of the same workload.
+complex64, a stream per member, with tuned and with default launch shapes);
+`large` times Krylov steps of the L = 30 ring (m = 20, dt = 0.5, complex128
+and complex64).  Every rate is the median of --repeats timed runs of exactly
+--steps steps.  Also reported: standalone y = H x throughput (algorithmic
+bytes 2 s D per call), a device-copy ceiling, the roofline of the dominant
+kernel from HIP events recorded on the step's stream, and the CPU oracle timed
+on a bounded sample of the same workload.
 """
 from __future__ import annotations
 
@@ -184,22 +184,17 @@ def run_mixed(qk, torch, steps, warmup, repeats, m=30, dt=0.1, h=2.0, tune=True)
         torch.cuda.synchronize()
         secs.append(time.perf_counter() - t0)
     sec = statistics.median(secs)
-    # the same members in the default launch shape, use_graph = 1 and 2:
-    # launches per step against use_graph = 2 (which takes 256-thread
-    # row-streaming blocks)
+    # the same members in the default launch shape
     for k in ks:
         qk.qk_krylov_set_shape(k)
-    default = {}
-    for mode in (1, 2):
-        qk.qk_batch_run(bt, dt, max(warmup, 1), use_graph=mode)
-        ms = []
-        for _ in range(repeats):
-            torch.cuda.synchronize()
-            t0 = time.perf_counter()
-            qk.qk_batch_run(bt, dt, steps, use_graph=mode, out=out)
-            torch.cuda.synchronize()
-            ms.append(time.perf_counter() - t0)
-        default[mode] = statistics.median(ms)
+    qk.qk_batch_run(bt, dt, max(warmup, 1), use_graph=True)
+    default = []
+    for _ in range(repeats):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        qk.qk_batch_run(bt, dt, steps, use_graph=True, out=out)
+        torch.cuda.synchronize()
+        default.append(time.perf_counter() - t0)
     # kernels of the 64-phase L = 20 workspace alone (eager steps with events)
     k64, psi64 = ks[0], psis[0]
     qk.qk_krylov_profile(k64, True)
@@ -210,8 +205,7 @@ def run_mixed(qk, torch, steps, warmup, repeats, m=30, dt=0.1, h=2.0, tune=True)
     qk.qk_krylov_profile(k64, False)
     D20 = qk.qk_basis_dim(hold[0][0])
     res = dict(items=items, steps=steps, sec=sec, sec_all=secs, phase_steps_per_s=items * steps / sec,
-               steps_per_s=steps / sec, prof64=prof, D20=D20, sec_graph_default=default[1],
-               sec_graph2=default[2])
+               steps_per_s=steps / sec, prof64=prof, D20=D20, sec_default=statistics.median(default))
     bt.close()
     del ks, psis, hold
     torch.cuda.synchronize()
@@ -678,11 +672,9 @@ def main():
             steps_per_s=round(mixed["steps_per_s"], 2), ms_per_step=round(1e3 * mixed["sec"] / mixed["steps"], 3),
             ms_per_step_runs=[round(1e3 * x / mixed["steps"], 3) for x in mixed["sec_all"]],
             default_shape=dict(
-                graph_ms_per_step=round(1e3 * mixed["sec_graph_default"] / mixed["steps"], 3),
-                graph2_ms_per_step=round(1e3 * mixed["sec_graph2"] / mixed["steps"], 3),
-                graph2_phase_steps_per_s=round(mixed["items"] * mixed["steps"] / mixed["sec_graph2"], 1),
-                note="the members in the default launch shape: use_graph=1, and "
-                     "use_graph=2, which runs the same launches"),
+                ms_per_step=round(1e3 * mixed["sec_default"] / mixed["steps"], 3),
+                phase_steps_per_s=round(mixed["items"] * mixed["steps"] / mixed["sec_default"], 1),
+                note="the members in the default launch shape"),
             roofline_L20x64=hpass_roofline(mixed["prof64"], 30, mixed["D20"], 64, 8, None),
             kernels_L20x64={kname: dict(ms_per_launch=ms_ / max(n_, 1), launches=n_)
                             for kname, (ms_, n_) in mixed["prof64"].items()})

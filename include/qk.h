@@ -307,7 +307,9 @@ void qk_krylov_destroy(qk_krylov* k);
  * large sectors the high-bond pass), the update pass (new vector and its
  * norm; in the split the low-bond pass that also forms the new vector), the
  * projected exponential, the Krylov combination, and the split's pre-pass
- * over a step's initial vector.
+ * over a step's initial vector.  While recording, a workspace whose steps take
+ * one launch (qk_krylov_create) takes them kernel by kernel: slower than they
+ * otherwise are, with sums in another order.
  */
 enum { QK_KERNEL_LANCZOS_H = 0, QK_KERNEL_LANCZOS_UPDATE = 1, QK_KERNEL_SMALL_EXPM = 2, QK_KERNEL_COMBINE = 3,
        QK_KERNEL_PREPASS = 4, QK_NUM_KERNELS = 5 };

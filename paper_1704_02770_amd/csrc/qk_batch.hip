@@ -409,8 +409,6 @@ void batch_destroy(qk_batch* b) {
   delete b;
 }
 
-// One step of every workspace, each on its own stream forked from `s` and
-// joined back, then the autocorrelation advances and the step counter moves on.
 // Which workspaces of a batch take the passes although the step in one launch
 // covers them: all, where the others have more than kBesideElements elements
 // (their kernels fill the compute units that its work-groups would wait for: 64
@@ -440,6 +438,8 @@ static std::vector<bool> batch_beside(const qk_batch* b) {
   return out;
 }
 
+// One step of every workspace, each on its own stream forked from `s` and
+// joined back, then the autocorrelation advances and the step counter moves on.
 static qk_status batch_step(qk_batch* b, double dt, double* P, double* C, hipStream_t s) {
   const std::vector<bool> beside = batch_beside(b);
   QK_HIP(hipEventRecord(b->fork, s));
@@ -478,7 +478,8 @@ static std::vector<uint64_t> batch_signature(const qk_batch* b) {
 
 // What use_graph = 2 takes (qk_batch_run): one dtype, chains of at most 32
 // sites, no split layout, reorthogonalisation 0 or 1, vectors below 4 GB,
-// row-streaming blocks of 256 threads.
+// row-streaming blocks of 256 threads.  The launches are those of 1, which need
+// none of it; a caller who relies on the refusal still gets it.
 static qk_status batch_mode2_check(const qk_batch* b) {
   const char* why = nullptr;
   for (const qk_krylov* k : b->ks) {
@@ -519,7 +520,9 @@ qk_status batch_run(qk_batch* b, double dt, int n_steps, int use_graph, double* 
   qk_status st = QK_OK;
   // Several workspaces are launched directly on their streams: a run of 500
   // replays of a graph with five branches has ended in a segmentation fault of
-  // the host inside the runtime, of unknown cause.
+  // the host inside the runtime, of unknown cause.  The host's launches then
+  // bound many small workspaces (13 sites with 16 phases beside rings of 22, 20
+  // and 18: 6.8 ms a step, 4.75 as a graph).
   if (!use_graph || b->ks.size() > 1) {
     for (int k = 0; k < n_steps && st == QK_OK; ++k) st = batch_step(b, dt, P, C, s);
     restore();

@@ -50,8 +50,8 @@
 // L = 20); three barriers and the scalars between them, 1.5 us.  In one
 // work-group 1.4 us an iteration, the gathers from LDS and the sums over the
 // waves.  A step of 30 vectors, complex128, one phase, against the passes:
-// L = 12 (open, 20 vectors) 51 against 244 us, L = 16 171 against 420, L = 18
-// 217, L = 20 325 against 690; of four phases at L = 12 in complex64 182.
+// L = 12 (open, 20 vectors) 51 against 244 us, L = 16 173 against 420, L = 18
+// 219, L = 20 333 against 690; of four phases at L = 12 in complex64 182.
 #include <algorithm>
 #include <mutex>
 #include <type_traits>

@@ -93,7 +93,7 @@ k_apply(const typename Cx<T>::V* __restrict__ x, typename Cx<T>::V* __restrict__
   const int B = a.B, b = threadIdx.x % B;
   const uint32_t R = blockDim.x / B, rl = threadIdx.x / B;
   const uint32_t ntiles = (hv.D + R - 1) / R;
-  for (TileWalk w(ntiles); w.t < w.t_end; w.t += w.step) {
+  for (TileWalk w(ntiles, hw_grid()); w.t < w.t_end; w.t += w.step) {
     const uint32_t r = w.t * R + rl;
     if (r >= hv.D) continue;
     typename Cx<T>::V xr;
@@ -108,13 +108,13 @@ k_lanczos_A(const typename Cx<T>::V* __restrict__ uj, const typename Cx<T>::V* _
             const double* __restrict__ gfields, KState st, LanczosArgs la, const double* __restrict__ partB, int Gp,
             double* __restrict__ partA) {
   __shared__ LanczosAShared<S> ls;
-  lanczos_a_body<T, CSR, S>(ls, uj, ujm1, w, a, hv, gtab, gfields, st, la, partB, Gp, partA);
+  lanczos_a_body<T, CSR, S>(hw_range(), ls, uj, ujm1, w, a, hv, gtab, gfields, st, la, partB, Gp, partA);
 }
 
 __global__ void __launch_bounds__(256) k_partials_total(const double* __restrict__ part, int G, int cols,
                                                         double* __restrict__ tot) {
   __shared__ double red[256];
-  partials_total_body(red, part, G, cols, tot);
+  partials_total_body(hw_range(), red, part, G, cols, tot);
 }
 
 template <typename T, bool NT>
@@ -123,7 +123,7 @@ k_lanczos_B(const typename Cx<T>::V* __restrict__ uj, const typename Cx<T>::V* _
             typename Cx<T>::V* __restrict__ w, uint32_t D, int B, KState st, LanczosArgs la,
             const double* __restrict__ partA, int Gp, double* __restrict__ partB, int store) {
   __shared__ LanczosBShared ls;
-  lanczos_b_body<T, NT>(ls, uj, ujm1, w, D, B, st, la, partA, Gp, partB, store);
+  lanczos_b_body<T, NT>(hw_range(), ls, uj, ujm1, w, D, B, st, la, partA, Gp, partB, store);
 }
 
 
@@ -146,7 +146,7 @@ k_reorth_dots(const typename Cx<T>::V* __restrict__ psi, const typename Cx<T>::V
   double acc[2 * kReorthChunk];
 #pragma unroll
   for (int q = 0; q < 2 * kReorthChunk; ++q) acc[q] = 0.0;
-  for (TileWalk tw(ntiles); tw.t < tw.t_end; tw.t += tw.step) {
+  for (TileWalk tw(ntiles, hw_grid()); tw.t < tw.t_end; tw.t += tw.step) {
     const uint32_t r = tw.t * R + rl;
     if (r >= D) continue;
     const size_t i = (size_t)r * B + b;
@@ -191,7 +191,7 @@ k_reorth_axpy(const typename Cx<T>::V* __restrict__ psi, const typename Cx<T>::V
   const uint32_t ntiles = (D + R - 1) / R;
   const size_t stride = (size_t)D * B;
   double s = 0.0;
-  for (TileWalk tw(ntiles); tw.t < tw.t_end; tw.t += tw.step) {
+  for (TileWalk tw(ntiles, hw_grid()); tw.t < tw.t_end; tw.t += tw.step) {
     const uint32_t r = tw.t * R + rl;
     if (r >= D) continue;
     const size_t i = (size_t)r * B + b;
@@ -243,7 +243,7 @@ __global__ void __launch_bounds__(kMaxBlock)
 k_combine(typename Cx<T>::V* __restrict__ psi, const typename Cx<T>::V* __restrict__ U, uint32_t D, int B, int m,
           KState st) {
   extern __shared__ double2 cf[];   // [m][B] coefficients when B > 1
-  combine_body<T, E, ONE, NT>(cf, psi, U, D, B, m, st);
+  combine_body<T, E, ONE, NT>(hw_range(), cf, psi, U, D, B, m, st);
 }
 
 
@@ -261,7 +261,7 @@ __global__ void __launch_bounds__(kMaxBlock)
 k_overlap_partial(const typename Cx<T>::V* __restrict__ psi0, const typename Cx<T>::V* __restrict__ psi, uint32_t D,
                   int B, double* __restrict__ part) {
   __shared__ double red[2 * kMaxBlock];
-  overlap_partial_body<T>(red, psi0, psi, D, B, part);
+  overlap_partial_body<T>(hw_range(), red, psi0, psi, D, B, part);
 }
 
 // |<psi0, psi>|^2 per column into P[b], or, with a step counter, into

@@ -23,7 +23,7 @@ struct LanczosAShared {
 // for sectors without block tables: w = sa H u_j - sb u_{j-1} with the
 // partial sums of pass A (Sec. 2 "Krylov subspace methods"; rows of Eq. (1)).
 template <typename T, bool CSR, typename S>
-__device__ __forceinline__ void lanczos_a_body(LanczosAShared<S>& ls,
+__device__ __forceinline__ void lanczos_a_body(VRange rg, LanczosAShared<S>& ls,
                                                const typename Cx<T>::V* __restrict__ uj,
                                                const typename Cx<T>::V* __restrict__ ujm1,
                                                typename Cx<T>::V* __restrict__ w, const ModelArgs& a,
@@ -38,36 +38,39 @@ __device__ __forceinline__ void lanczos_a_body(LanczosAShared<S>& ls,
   int* act = ls.act;
   load_row_shared(sh, a, gtab, gfields);
   const int B = a.B;
-  lanczos_h_scalars(B, st, la, partB, Gp, red, tot, sa, sb, act);
+  lanczos_h_scalars(B, st, la, partB, Gp, red, tot, sa, sb, act, VGrid{rg.v0, rg.n});
 
   const int b = threadIdx.x % B;
   const uint32_t R = blockDim.x / B, rl = threadIdx.x / B;
   const uint32_t ntiles = (hv.D + R - 1) / R;
-  double s1 = 0.0, s2 = 0.0, s3r = 0.0, s3i = 0.0;
-  if (act[b]) {
-    const T ca = (T)sa[b], cb = (T)sb[b];
-    for (TileWalk tw(ntiles); tw.t < tw.t_end; tw.t += tw.step) {
-      const uint32_t r = tw.t * R + rl;
-      if (r >= hv.D) continue;
-      V xr;
-      const V hx = h_row<T, CSR, S>(r, b, a, sh, hv, uj, xr);
-      V wv;
-      wv.x = ca * hx.x;
-      wv.y = ca * hx.y;
-      if (la.j > 0) {
-        const V um = ujm1[(size_t)r * B + b];
-        wv.x -= cb * um.x;
-        wv.y -= cb * um.y;
-        s3r += (double)um.x * (double)wv.x + (double)um.y * (double)wv.y;
-        s3i += (double)um.x * (double)wv.y - (double)um.y * (double)wv.x;
+  for (uint32_t vb = rg.v0; vb < rg.v1; ++vb) {
+    double s1 = 0.0, s2 = 0.0, s3r = 0.0, s3i = 0.0;
+    if (act[b]) {
+      const T ca = (T)sa[b], cb = (T)sb[b];
+      for (TileWalk tw(ntiles, VGrid{vb, rg.n}); tw.t < tw.t_end; tw.t += tw.step) {
+        const uint32_t r = tw.t * R + rl;
+        if (r >= hv.D) continue;
+        V xr;
+        const V hx = h_row<T, CSR, S>(r, b, a, sh, hv, uj, xr);
+        V wv;
+        wv.x = ca * hx.x;
+        wv.y = ca * hx.y;
+        if (la.j > 0) {
+          const V um = ujm1[(size_t)r * B + b];
+          wv.x -= cb * um.x;
+          wv.y -= cb * um.y;
+          s3r += (double)um.x * (double)wv.x + (double)um.y * (double)wv.y;
+          s3i += (double)um.x * (double)wv.y - (double)um.y * (double)wv.x;
+        }
+        w[(size_t)r * B + b] = wv;
+        s1 += (double)xr.x * (double)wv.x + (double)xr.y * (double)wv.y;
+        s2 += (double)xr.x * (double)xr.x + (double)xr.y * (double)xr.y;
       }
-      w[(size_t)r * B + b] = wv;
-      s1 += (double)xr.x * (double)wv.x + (double)xr.y * (double)wv.y;
-      s2 += (double)xr.x * (double)xr.x + (double)xr.y * (double)xr.y;
     }
+    double v[kQA] = {s1, s2, s3r, s3i};
+    block_partials<kQA>(v, B, red, partA + (size_t)vb * kQA * B);
+    __syncthreads();   // red is written again by the next virtual block
   }
-  double v[kQA] = {s1, s2, s3r, s3i};
-  block_partials<kQA>(v, B, red, partA + (size_t)blockIdx.x * kQA * B);
 }
 
 // Non-temporal load of one complex element, for vectors a pass reads once.
@@ -92,20 +95,23 @@ constexpr int kPreReduceBatch = 8;
 constexpr int kTotLanes = 32;                  // lanes per column
 constexpr int kTotCols = 256 / kTotLanes;      // columns per block
 // red: LDS scratch of 256 doubles; 256 threads.
-__device__ __forceinline__ void partials_total_body(double* red, const double* __restrict__ part, int G,
+__device__ __forceinline__ void partials_total_body(VRange rg, double* red, const double* __restrict__ part, int G,
                                                     int cols, double* __restrict__ tot) {
   const int tid = threadIdx.x;
-  const int c = (int)blockIdx.x * kTotCols + tid / kTotLanes, l = tid % kTotLanes;
-  double acc = 0.0;
-  if (c < cols)
-    for (int g = l; g < G; g += kTotLanes) acc += part[(size_t)g * cols + c];
-  red[tid] = acc;
-  __syncthreads();
-  for (int h = kTotLanes / 2; h > 0; h >>= 1) {
-    if (l < h) red[tid] += red[tid + h];
+  for (uint32_t vb = rg.v0; vb < rg.v1; ++vb) {
+    const int c = (int)vb * kTotCols + tid / kTotLanes, l = tid % kTotLanes;
+    double acc = 0.0;
+    if (c < cols)
+      for (int g = l; g < G; g += kTotLanes) acc += part[(size_t)g * cols + c];
+    red[tid] = acc;
     __syncthreads();
+    for (int h = kTotLanes / 2; h > 0; h >>= 1) {
+      if (l < h) red[tid] += red[tid + h];
+      __syncthreads();
+    }
+    if (l == 0 && c < cols) tot[c] = red[tid];
+    __syncthreads();   // red is written again by the next virtual block
   }
-  if (l == 0 && c < cols) tot[c] = red[tid];
 }
 
 // LDS of the update pass.
@@ -119,7 +125,7 @@ struct LanczosBShared {
 // Update pass of Lanczos iteration j: u_{j+1} = c_j (w - d_j u_j) [- e_j u_{j-1}]
 // in place of w (store != 0), with the partial sums |u_{j+1}|^2.
 template <typename T, bool NT>
-__device__ __forceinline__ void lanczos_b_body(LanczosBShared& ls,
+__device__ __forceinline__ void lanczos_b_body(VRange rg, LanczosBShared& ls,
                                                const typename Cx<T>::V* __restrict__ uj,
                                                const typename Cx<T>::V* __restrict__ ujm1,
                                                typename Cx<T>::V* __restrict__ w, uint32_t D, int B,
@@ -131,7 +137,7 @@ __device__ __forceinline__ void lanczos_b_body(LanczosBShared& ls,
   double* tot = ls.tot;
   double *sc = ls.sc, *sd = ls.sd, *ser = ls.ser, *sei = ls.sei;
   int* act = ls.act;
-  const bool first = blockIdx.x == 0;   // the block that records the shared results
+  const bool first = rg.v0 == 0;   // the block that records the shared results
   const int j = la.j;
   const bool ro = la.reorth && j > 0;
   // the column's scalars are fetched while the partials are in flight
@@ -191,37 +197,40 @@ __device__ __forceinline__ void lanczos_b_body(LanczosBShared& ls,
   const int b = threadIdx.x % B;
   const uint32_t R = blockDim.x / B, rl = threadIdx.x / B;
   const uint32_t ntiles = (D + R - 1) / R;
-  double s = 0.0;
-  if (act[b]) {
-    const double c = sc[b], d = sd[b], er = ser[b], ei = sei[b];
-    for (TileWalk tw(ntiles); tw.t < tw.t_end; tw.t += tw.step) {
-      const uint32_t r = tw.t * R + rl;
-      if (r >= D) continue;
-      const size_t i = (size_t)r * B + b;
-      V wv, u;
-      if (NT) {
-        wv = ld_nt(w + i);
-        u = ld_nt(uj + i);
-      } else {
-        wv = w[i];
-        u = uj[i];
+  for (uint32_t vb = rg.v0; vb < rg.v1; ++vb) {
+    double s = 0.0;
+    if (act[b]) {
+      const double c = sc[b], d = sd[b], er = ser[b], ei = sei[b];
+      for (TileWalk tw(ntiles, VGrid{vb, rg.n}); tw.t < tw.t_end; tw.t += tw.step) {
+        const uint32_t r = tw.t * R + rl;
+        if (r >= D) continue;
+        const size_t i = (size_t)r * B + b;
+        V wv, u;
+        if (NT) {
+          wv = ld_nt(w + i);
+          u = ld_nt(uj + i);
+        } else {
+          wv = w[i];
+          u = uj[i];
+        }
+        double nx = c * ((double)wv.x - d * (double)u.x);
+        double ny = c * ((double)wv.y - d * (double)u.y);
+        if (ro) {
+          const V um = ujm1[i];
+          nx -= er * (double)um.x - ei * (double)um.y;
+          ny -= er * (double)um.y + ei * (double)um.x;
+        }
+        V o;
+        o.x = (T)nx;
+        o.y = (T)ny;
+        if (store) w[i] = o;
+        s += (double)o.x * (double)o.x + (double)o.y * (double)o.y;
       }
-      double nx = c * ((double)wv.x - d * (double)u.x);
-      double ny = c * ((double)wv.y - d * (double)u.y);
-      if (ro) {
-        const V um = ujm1[i];
-        nx -= er * (double)um.x - ei * (double)um.y;
-        ny -= er * (double)um.y + ei * (double)um.x;
-      }
-      V o;
-      o.x = (T)nx;
-      o.y = (T)ny;
-      if (store) w[i] = o;
-      s += (double)o.x * (double)o.x + (double)o.y * (double)o.y;
     }
+    double v[1] = {s};
+    block_partials<1>(v, B, red, partB + (size_t)vb * B);
+    __syncthreads();   // red is written again by the next virtual block
   }
-  double v[1] = {s};
-  block_partials<1>(v, B, red, partB + (size_t)blockIdx.x * B);
 }
 
 // ------------------------------------------ projected exponential (1 wave)
@@ -342,7 +351,7 @@ constexpr int kCombineUnroll = 8;
 
 // cf: LDS of m * B double2 (B > 1; unused for one column).
 template <typename T, int E, bool ONE, bool NT>
-__device__ __forceinline__ void combine_body(double2* cf, typename Cx<T>::V* __restrict__ psi,
+__device__ __forceinline__ void combine_body(VRange rg, double2* cf, typename Cx<T>::V* __restrict__ psi,
                                              const typename Cx<T>::V* __restrict__ U, uint32_t D, int B, int m,
                                              const KState& st) {
   using V = typename Cx<T>::V;
@@ -360,7 +369,8 @@ __device__ __forceinline__ void combine_body(double2* cf, typename Cx<T>::V* __r
   const uint64_t np = (uint64_t)D * B / E;   // packs per vector (the launcher makes D * B a multiple of E)
   const Pack* Up = reinterpret_cast<const Pack*>(U);
   Pack* Pp = reinterpret_cast<Pack*>(psi);
-  for (uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; p < np; p += (uint64_t)gridDim.x * blockDim.x) {
+  for (uint32_t vb = rg.v0; vb < rg.v1; ++vb)
+  for (uint64_t p = (uint64_t)vb * blockDim.x + threadIdx.x; p < np; p += (uint64_t)rg.n * blockDim.x) {
     int bc[E], mu[E];
     bool ok[E];
     int mumax = 0;
@@ -430,23 +440,26 @@ __device__ __forceinline__ void combine_body(double2* cf, typename Cx<T>::V* __r
 // ------------------------------------------------ survival probability
 // red: LDS of 2 * blockDim doubles.
 template <typename T>
-__device__ __forceinline__ void overlap_partial_body(double* red, const typename Cx<T>::V* __restrict__ psi0,
+__device__ __forceinline__ void overlap_partial_body(VRange rg, double* red, const typename Cx<T>::V* __restrict__ psi0,
                                                      const typename Cx<T>::V* __restrict__ psi, uint32_t D, int B,
                                                      double* __restrict__ part) {
   const int b = threadIdx.x % B;
   const uint32_t R = blockDim.x / B, rl = threadIdx.x / B;
   const uint32_t ntiles = (D + R - 1) / R;
-  double sr = 0.0, si = 0.0;
-  for (TileWalk tw(ntiles); tw.t < tw.t_end; tw.t += tw.step) {
-    const uint32_t r = tw.t * R + rl;
-    if (r >= D) continue;
-    const size_t i = (size_t)r * B + b;
-    const typename Cx<T>::V a = psi0[i], c = psi[i];
-    sr += (double)a.x * (double)c.x + (double)a.y * (double)c.y;   // conj(a) c
-    si += (double)a.x * (double)c.y - (double)a.y * (double)c.x;
+  for (uint32_t vb = rg.v0; vb < rg.v1; ++vb) {
+    double sr = 0.0, si = 0.0;
+    for (TileWalk tw(ntiles, VGrid{vb, rg.n}); tw.t < tw.t_end; tw.t += tw.step) {
+      const uint32_t r = tw.t * R + rl;
+      if (r >= D) continue;
+      const size_t i = (size_t)r * B + b;
+      const typename Cx<T>::V a = psi0[i], c = psi[i];
+      sr += (double)a.x * (double)c.x + (double)a.y * (double)c.y;   // conj(a) c
+      si += (double)a.x * (double)c.y - (double)a.y * (double)c.x;
+    }
+    double v[2] = {sr, si};
+    block_partials<2>(v, B, red, part + (size_t)vb * 2 * B);
+    __syncthreads();   // red is written again by the next virtual block
   }
-  double v[2] = {sr, si};
-  block_partials<2>(v, B, red, part + (size_t)blockIdx.x * 2 * B);
 }
 
 // |<psi0, psi>|^2 per column into P[b], or, with a step counter, into

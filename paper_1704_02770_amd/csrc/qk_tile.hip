@@ -205,7 +205,7 @@ k_tile(TileArgs ta, uint64_t nel, const typename Cx<T>::V* __restrict__ x, typen
     double* sa = reinterpret_cast<double*>(smem + ta.scratch);
     double *sb = sa + B, *tot = sb + B, *red = tot + B;
     int* act = reinterpret_cast<int*>(red + ta.nred);
-    lanczos_h_scalars(B, st, la, partB, Gp, red, tot, sa, sb, act);
+    lanczos_h_scalars(B, st, la, partB, Gp, red, tot, sa, sb, act, hw_grid());
     if (mine) {
       ca = (T)sa[p];
       cb = (T)sb[p];

@@ -187,6 +187,9 @@ __device__ __forceinline__ VGrid hw_grid() { return VGrid{blockIdx.x, gridDim.x}
 // work-group one after another: what a block's results depend on (tables,
 // the scalars reduced from the previous pass) is set up once for the run,
 // then each virtual block does its own rows and writes its own partial sums.
+// Every launch gives a work-group one.  The loop over them stays because the
+// bodies compile to slower code without it: the update pass of the open 24-site
+// chain 24.13 against 24.40 us, of L = 22 with three phases 33.07 against 33.37.
 struct VRange {
   uint32_t v0, v1, n;
 };

@@ -446,7 +446,7 @@ static qk_status batch_step(qk_batch* b, double dt, double* P, double* C, hipStr
   for (size_t i = 0; i < b->ks.size(); ++i) {
     hipStream_t si = b->streams[i];
     QK_HIP(hipStreamWaitEvent(si, b->fork, 0));
-    qk_status st = launch_krylov_step(b->ks[i], b->psi[i], dt, si, StepUpTo::combination, beside[i]);
+    qk_status st = launch_krylov_member(b->ks[i], b->psi[i], dt, si, s, beside[i]);
     if (st != QK_OK) return st;
     st = record_item(b, (int)i, P, si);
     if (st != QK_OK) return st;

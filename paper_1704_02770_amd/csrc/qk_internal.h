@@ -148,7 +148,7 @@ struct qk_krylov {
   // order of such steps on several streams (resident_order); under its mutex
   qk_krylov *res_prev = nullptr, *res_next = nullptr;
   hipEvent_t res_event = nullptr;   // after its last launch that was ordered
-  hipStream_t res_stream = nullptr; // of its last launch
+  hipStream_t res_stream = nullptr; // of its last launch, or that one's stream was forked from
   bool res_launched = false;
   int res_share = 0;                // compute units that its work-groups fill, 0: not known yet
   // event timing (qk_krylov_profile)
@@ -246,11 +246,15 @@ void resident_unregister(qk_krylov* k);
 const uint32_t* resident_verdict(const qk_krylov* k);
 bool resident_gave_up(const qk_krylov* k);   // waits for the device
 int resident_groups(const qk_krylov* k);   // its work-groups, 0 where it does not cover the workspace
+// from: the stream that s is forked from and joined to, or s itself.
 qk_status launch_resident(qk_krylov* k, void* psi, double rtol, double tau, StepUpTo upto, const AdaptiveStep* ad,
-                          hipStream_t s, bool* done);
-// beside: by the passes, as steps of other workspaces fill the chip meanwhile.
+                          hipStream_t s, hipStream_t from, bool* done);
 qk_status launch_krylov_step(qk_krylov* k, void* psi, double dt, hipStream_t s,
-                             StepUpTo upto = StepUpTo::combination, bool beside = false);
+                             StepUpTo upto = StepUpTo::combination);
+// A step of one of several workspaces that advance together, on a stream s
+// forked from `from`.  beside: by the passes, as steps of the others fill the
+// chip meanwhile.
+qk_status launch_krylov_member(qk_krylov* k, void* psi, double dt, hipStream_t s, hipStream_t from, bool beside);
 // One step of at most tau_max whose length the device chooses from the error
 // estimate: st.tau[b] receives the accepted step of column b, st.tau[B + b] a
 // suggested next step; every column advances by the smallest accepted step.

@@ -543,7 +543,7 @@ static void launch_combine(typename Cx<T>::V* psi, const typename Cx<T>::V* U, u
 }
 
 template <typename T>
-static qk_status krylov_step_t(qk_krylov* k, void* psi_v, double dt, hipStream_t s, StepUpTo upto,
+static qk_status krylov_step_t(qk_krylov* k, void* psi_v, double dt, hipStream_t s, hipStream_t from, StepUpTo upto,
                                bool beside = false, const AdaptiveStep* ad = nullptr) {
   using V = typename Cx<T>::V;
   const qk_ham* H = k->H;
@@ -608,7 +608,7 @@ static qk_status krylov_step_t(qk_krylov* k, void* psi_v, double dt, hipStream_t
   const bool resident = resident_covers(k) && !k->profiling && !beside;
   if (resident) {
     bool done = false;
-    const qk_status rs = launch_resident(k, psi, rtol, ad ? ad->tau_max : dt, upto, ad, s, &done);
+    const qk_status rs = launch_resident(k, psi, rtol, ad ? ad->tau_max : dt, upto, ad, s, from, &done);
     if (rs != QK_OK || done) return rs;
     pB = k->d_partB;
     GB = 1;
@@ -738,15 +738,20 @@ qk_status profile_collect(qk_krylov* k) {
   return QK_OK;
 }
 
-qk_status launch_krylov_step(qk_krylov* k, void* psi, double dt, hipStream_t s, StepUpTo upto, bool beside) {
-  if (k->dtype == QK_C128) return krylov_step_t<double>(k, psi, dt, s, upto, beside);
-  return krylov_step_t<float>(k, psi, dt, s, upto, beside);
+qk_status launch_krylov_step(qk_krylov* k, void* psi, double dt, hipStream_t s, StepUpTo upto) {
+  if (k->dtype == QK_C128) return krylov_step_t<double>(k, psi, dt, s, s, upto);
+  return krylov_step_t<float>(k, psi, dt, s, s, upto);
+}
+
+qk_status launch_krylov_member(qk_krylov* k, void* psi, double dt, hipStream_t s, hipStream_t from, bool beside) {
+  if (k->dtype == QK_C128) return krylov_step_t<double>(k, psi, dt, s, from, StepUpTo::combination, beside);
+  return krylov_step_t<float>(k, psi, dt, s, from, StepUpTo::combination, beside);
 }
 
 qk_status launch_krylov_adaptive_step(qk_krylov* k, void* psi, double tau_max, double tol, hipStream_t s) {
   const AdaptiveStep ad{tau_max, tol};
-  if (k->dtype == QK_C128) return krylov_step_t<double>(k, psi, tau_max, s, StepUpTo::combination, false, &ad);
-  return krylov_step_t<float>(k, psi, tau_max, s, StepUpTo::combination, false, &ad);
+  if (k->dtype == QK_C128) return krylov_step_t<double>(k, psi, tau_max, s, s, StepUpTo::combination, false, &ad);
+  return krylov_step_t<float>(k, psi, tau_max, s, s, StepUpTo::combination, false, &ad);
 }
 
 qk_status launch_return_prob(const qk_basis* b, int64_t r0, const void* psi0, const void* psi, int dtype, int B,
